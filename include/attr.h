@@ -210,7 +210,9 @@ attr_status attr_precond_accumulate(const void* X, attr_dtype x_dtype, int64_t n
  *   Y = y cast to y_dtype (round to nearest even).
  * FULL evaluates M as a scaled fp16 pair, A = 2^s M (max|A| <= 2^15),
  * A_hi = fp16(A), A_lo = fp16(A - A_hi), y = 2^-s X (A_hi + A_lo)^T on fp16
- * MFMA with fp32 accumulation (about 22 significant bits of M).
+ * MFMA with fp32 accumulation (about 22 significant bits of M).  Few rows (a
+ * session's queries: up to 2^23 / D, and at most D) take a path that reads M
+ * once and scales each of its rows on its own.
  *
  *   X, ldx   device [n_rows, D], x_dtype ATTR_F32 or ATTR_F16
  *            (FULL: ATTR_F16 only)

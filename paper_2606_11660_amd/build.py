@@ -22,7 +22,8 @@ LIB = os.path.join(PKG, "libattr.so")
 ARCH = "gfx950"
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
-HIP_SOURCES = ["project.hip", "rowwise.hip", "syrk.hip", "apply_full.hip", "score.hip", "probe.hip"]
+HIP_SOURCES = ["project.hip", "rowwise.hip", "syrk.hip", "apply_full.hip", "apply_few.hip",
+               "score.hip", "probe.hip"]
 CXX_SOURCES = ["api.cpp"]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", f"-I{INCLUDE}", f"-I{CSRC}", "-Wall",

@@ -151,6 +151,21 @@ hipError_t launch_apply_full(const void* X, int64_t n_rows, int64_t ldx, int64_t
                              int y_dtype, void* Y, int64_t ldy, int unit, void* ws,
                              hipStream_t s);
 
+// FULL apply on few rows (apply_few.hip): M read once straight from the
+// caller, fp32 partials per K-slice in the workspace.  use: this row count
+// takes that path (the rule and its measurements are at plan_apply_few).
+struct ApplyFewPlan {
+  bool use;
+  int xt;                 // 16-row tiles of X per wave
+  int n_ct, n_sl, n_rb;   // column tiles, K-slices, row blocks
+  size_t part_bytes;      // fp32 partials, then
+  size_t pack_bytes;      // X in fragment order (0: read in place)
+};
+ApplyFewPlan plan_apply_few(int64_t n_rows, int64_t D);
+hipError_t launch_apply_few(const ApplyFewPlan& P, const void* X, int64_t n_rows, int64_t ldx,
+                            int64_t D, const float* M, int y_dtype, void* Y, int64_t ldy, int unit,
+                            void* ws, hipStream_t s);
+
 // ---------------------------------------------------------------------------
 // calibration
 // ---------------------------------------------------------------------------
