@@ -420,8 +420,7 @@ attr_status attr_precond_accumulate(const void* X, attr_dtype x_dtype, int64_t n
 // ---------------------------------------------------------------------------
 size_t attr_precond_apply_workspace_size(int64_t n_rows, int64_t D, attr_precond mode) {
   if (mode != ATTR_PRECOND_FULL || n_rows <= 0 || D < 1) return 0;
-  const attr::ApplyFewPlan few = attr::plan_apply_few(n_rows, D);
-  return few.use ? few.part_bytes + few.pack_bytes : attr::apply_full_workspace(n_rows, D, 1);
+  return attr::apply_full_workspace(n_rows, D, 1);  // the few-row path fits in it
 }
 
 attr_status attr_precond_apply(const void* X, attr_dtype x_dtype, int64_t n_rows, int64_t D,
@@ -461,15 +460,13 @@ attr_status attr_precond_apply(const void* X, attr_dtype x_dtype, int64_t n_rows
     if (n_rows > (1ll << 31) - 1) return fail(ATTR_ERR_UNSUPPORTED, "n_rows exceeds one launch");
     if (full) {
       if (ldx * 256 * 2 >= (1ll << 31)) return fail(ATTR_ERR_UNSUPPORTED, "row stride too large");
-      const attr::ApplyFewPlan few = attr::plan_apply_few(n_rows, D);
-      const size_t need =
-          few.use ? few.part_bytes + few.pack_bytes
-                   : attr::apply_full_workspace(n_rows, D, unit_normalize ? 1 : 0);
+      const size_t need = attr::apply_full_workspace(n_rows, D, unit_normalize ? 1 : 0);
       if (!ws || ws_bytes < need)
         return fail(ATTR_ERR_WORKSPACE, "attr_precond_apply (FULL) needs %zu workspace bytes", need);
       if (reinterpret_cast<uintptr_t>(ws) & 255u)
         return fail(ATTR_ERR_ALIGNMENT, "workspace must be 256-byte aligned");
       const hipStream_t st = static_cast<hipStream_t>(stream);
+      const attr::ApplyFewPlan few = attr::plan_apply_few(n_rows, D);
       hipError_t e = few.use ? attr::launch_apply_few(few, X, n_rows, ldx, D, M, (int)y_dtype, Y, ldy,
                                                       unit_normalize ? 1 : 0, ws, st)
                              : attr::launch_apply_full(X, n_rows, ldx, D, M, (int)y_dtype, Y, ldy,

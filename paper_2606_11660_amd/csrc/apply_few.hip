@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void apply_few_final_kernel(const float* __res
 
 // Calls that take this path: up to 2^23 values of X, where the general path's
 // passes over M and its part-filled GEMM still cost more, and no more rows
-// than D, so that the partials stay within 4 D^2 bytes.  At
+// than D, so that the partials fit the general path's workspace.  At
 // D = 8192: 1 / 64 / 256 / 1024 rows take 51 / 59 / 103 / 352 us here (5.2 /
 // 4.5 / 2.6 TB/s of M for the first three) and 390-420 us there; from 1536
 // rows the general path is as fast (474 us, here 503).  At D = 4096: 193 us
@@ -375,14 +375,20 @@ ApplyFewPlan plan_apply_few(int64_t n_rows, int64_t D) {
   P.xt = n_rows <= 64 ? 1 : (n_rows <= 128 ? 2 : 4);
   P.n_rb = (int)((n_rows + 64 * P.xt - 1) / (64 * P.xt));
   P.n_ct = (int)(D / FCOL);
+  // The workspace is the general path's (at least 4 D^2 bytes): partials and
+  // packed rows stay within that.  Up to 16 rows only one wave pair loads X:
+  // packing is not worth a launch.
+  const int64_t xrows = (int64_t)P.n_rb * 64 * P.xt;
+  const bool pack = n_rows > 16 && 4 * n_rows + 2 * xrows <= 4 * D;
+  const int64_t room = 4 * D - (pack ? 2 * xrows : 0);  // partial bytes per column, all slices
   // K-slices (whole groups of FPD stages): the count with the least modelled
   // time, in stages: whole rounds of one workgroup per CU, each the stages of
   // a slice plus ~6 to start and end, plus writing and reading one partial
-  // per slice (~7 MB per stage time).  Partials no larger than M itself.
+  // per slice (~7 MB per stage time).
   const int64_t n_gr = (D / FKS + FPD - 1) / FPD;
   int64_t best = INT64_MAX;
   P.n_sl = 1;
-  for (int64_t sl = 1; sl <= n_gr && sl <= 64 && sl * n_rows <= D; ++sl) {
+  for (int64_t sl = 1; sl <= n_gr && sl <= 64 && 4 * sl * n_rows <= room; ++sl) {
     const int64_t rounds = (sl * P.n_ct * P.n_rb + 255) / 256;
     const int64_t cost = rounds * (FPD * ((n_gr + sl - 1) / sl) + 6) + sl * n_rows * D * 8 / 7000000;
     if (cost < best) {
@@ -390,10 +396,8 @@ ApplyFewPlan plan_apply_few(int64_t n_rows, int64_t D) {
       P.n_sl = (int)sl;
     }
   }
-  P.part_bytes = ((size_t)P.n_sl * (size_t)n_rows * (size_t)D * 4 + 255) / 256 * 256;
-  // up to 16 rows only one wave pair loads X: not worth a launch
-  const size_t xrows = (size_t)P.n_rb * 64 * (size_t)P.xt;
-  P.pack_bytes = n_rows > 16 ? xrows * (size_t)D * 2 : 0;
+  P.part_bytes = (size_t)P.n_sl * (size_t)n_rows * (size_t)D * 4;
+  P.pack_bytes = pack ? (size_t)xrows * (size_t)D * 2 : 0;
   return P;
 }
 
