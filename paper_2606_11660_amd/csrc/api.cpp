@@ -134,7 +134,9 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   }
   off += pk;
   L.off_part = off;
-  off += align_up((size_t)n_mods * (size_t)L.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
+  // per-token blocks have no partials; without them the ungrouped call's larger
+  // group table fits what the query (which does not know the call) returns
+  if (!tok) off += align_up((size_t)n_mods * (size_t)L.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
   L.total = off;
   return L;
 }

@@ -83,7 +83,23 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
                                int32_t* wl_perm, int32_t* wl_off,
                                float* partial, hipStream_t s, bool tok = false, int64_t ldo = 0,
                                int64_t n_rows = 0);
-hipError_t launch_project_reduce(int nk, const ProjTab* tab, int n_slots, int n_chunks,
+// Calls with few items: chunks of ct tokens, the contraction split over the
+// waves of a workgroup (ct = 0: the call takes the general kernel).
+struct ProjFewPlan {
+  int ct, n_chunks;
+};
+// group_cost, slot_cost: widths of the rows read per token, with a counted once
+// per group or once per module; longest: the largest group's; ragged: lengths
+// are given.
+ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64_t slot_cost, int64_t longest,
+                             int64_t n_slots, int64_t n_ex, int64_t T, bool ragged);
+// dst: the output (tok, or a single chunk per example) or the partials
+// [slot][chunk][example][k k].
+hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, const ProjTab* tab, int n_slots,
+                              int64_t n_ex, int64_t T, const int64_t* row_offset, const int32_t* length,
+                              float* dst, bool tok, int64_t ldo, int64_t n_rows, hipStream_t s);
+// CT: tokens per chunk
+hipError_t launch_project_reduce(int nk, int CT, const ProjTab* tab, int n_slots, int n_chunks,
                                  int64_t n_ex, int64_t T, const int32_t* length,
                                  const float* partial, float* out, int64_t ldo,
                                  hipStream_t s);

@@ -55,18 +55,18 @@ struct ElemT<false> {
   static constexpr int bytes = 4;
 };
 
-// Token tiles (16 tokens) per wave and load steps kept in flight, per
-// fragment width NK (k = 16 NK).
-#ifndef ATTR_PROJ_TT1
-#define ATTR_PROJ_TT1 4
-#endif
-#ifndef ATTR_PROJ_PD
-#define ATTR_PROJ_PD 3
-#endif
+// Token tiles (16 tokens) per wave, load steps kept in flight and waves per
+// SIMD, per fragment width NK (k = 16 NK).  Every wave reads the fragments of R
+// and S for its own tokens from L2, 32 NK bytes a K element in bf16 against
+// 32 TT of the token rows: four tiles keep that at k = 32 and 64 to half and
+// all of the rows' bytes, at one wave per SIMD (two and one tile, two waves:
+// 32 GPT-2-shaped examples x 512 tokens in bf16 890 -> 815 us at k = 32 and
+// 1540 -> 1051 us at k = 64).
 template <int NK>
 struct Tiles {
-  static constexpr int TT = NK == 1 ? ATTR_PROJ_TT1 : (NK == 2 ? 2 : 1);
-  static constexpr int PD = ATTR_PROJ_PD;
+  static constexpr int TT = 4;
+  static constexpr int PD = 3;
+  static constexpr int WPS = NK == 1 ? 2 : 1;
 };
 
 // bf16 bit pattern <-> float (bf16 is the upper half of an fp32 pattern);
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(1024) void project_worklist_kernel(const int32_t* _
 // The group size is read from the group table and dispatched at run time
 // (uniform per workgroup); every size fits two waves per SIMD.
 template <bool BF16, int NK, bool TOK>
-__global__ __launch_bounds__(256, 2) void project_main_kernel(
+__global__ __launch_bounds__(256, Tiles<NK>::WPS) void project_main_kernel(
     const ProjTab* __restrict__ tab, const ProjGroup* __restrict__ gtab, int n_groups,
     int n_chunks, int64_t n_ex, int64_t T, const int64_t* __restrict__ row_offset,
     const int32_t* __restrict__ length, const int32_t* __restrict__ wl_perm,
@@ -556,18 +556,251 @@ __global__ __launch_bounds__(256, 2) void project_main_kernel(
                                    partial, ldo, n_rows, xpose, red);
 }
 
+// Partial element e = ((rt*NK + ct)*4 + q)*64 + lane of a k x k block holds
+// r = 16 rt + 4 (lane / 16) + q, c = 16 ct + lane % 16: its place r k + c.
+template <int NK>
+__device__ inline int block_pos(int e) {
+  const int lane = e & 63, q = (e >> 6) & 3, tile = e >> 8;
+  const int r = 16 * (tile / NK) + 4 * (lane >> 4) + q;
+  return r * (16 * NK) + 16 * (tile % NK) + (lane & 15);
+}
+
+// ---------------------------------------------------------------------------
+// few items: the contraction split over the waves
+// ---------------------------------------------------------------------------
+// With few token rows (a query, a short batch) the kernel above is a serial
+// chain: ceil(tokens / 256) workgroups per module group, each of whose waves
+// walks all of d_in + d_out, a memory latency per few 128-byte groups, while
+// most of the chip is idle.  Here a workgroup takes 16 TT tokens of one module
+// and its four waves take a quarter of the K-groups each (the a side's quarter,
+// then the g side's, in one sequence, so that the loads of g are in flight
+// before a is finished); the projected tiles of the four waves are added in
+// LDS in wave order, and each wave contracts a quarter of the tokens.  The
+// chain is a quarter as long, and there are four times as many workgroups (TT
+// as above) or more (TT = 1).  Fragments of R and S are loaded as far ahead as
+// the token rows.  Modules are not grouped: with few workgroups, reading a
+// shared a again costs less than one long item.  Loads past the end are issued
+// from outside the descriptors' ranges (zeros, no memory access), so every
+// iteration issues the same loads and the compiler counts the loads in flight
+// instead of draining them at a branch.
+template <int NK, int TT>
+struct FewTiles {
+  // stages in flight: (8 TT + 8 NK) registers each.  Two waves per SIMD also
+  // at k = 64, where 36 registers spill (16384 tokens: 613 us; 645 and 669 with
+  // one wave and three or four stages).
+  static constexpr int PD = 160 / (8 * TT + 8 * NK) > 8 ? 8 : 160 / (8 * TT + 8 * NK);
+
+};
+
+// direct: a single chunk per example, whose block goes to its place in the
+// output (dst, row stride ldo) instead of to a partial.
+template <bool BF16, int NK, int TT, bool TOK>
+__global__ __launch_bounds__(256, 2) void project_few_kernel(
+    const ProjTab* __restrict__ tab, int n_chunks, int64_t n_ex, int64_t T,
+    const int64_t* __restrict__ row_offset, const int32_t* __restrict__ length,
+    float* __restrict__ dst, int64_t ldo, int64_t n_rows, int direct) {
+  using E_t = ElemT<BF16>;
+  using Tag = typename E_t::tag;
+  constexpr int EB = E_t::bytes;
+  constexpr int KG = 128 / EB;  // K elements per 128-byte group
+  constexpr int K = 16 * NK, KK = K * K;
+  constexpr int CT = 16 * TT;
+  constexpr int PD = FewTiles<NK, TT>::PD;
+  constexpr int XP = TT * 128;       // 16-byte slots of a wave's transpose tile
+  constexpr int PT = TT * NK;        // projected 16 x 16 tiles of a wave and side (1 KB each)
+  constexpr int SH = XP > PT * kWave ? XP : PT * kWave;
+  __shared__ i32x4 sh[4 * (SH > KK / 4 ? SH : KK / 4)];
+
+  const uint32_t nex = (uint32_t)n_ex, blk = blockIdx.x;
+  // the example index rotates as in the dense decode above
+  const uint32_t rest = blk / nex;
+  const int c = (int)(rest % (uint32_t)n_chunks), s = (int)(rest / (uint32_t)n_chunks);
+  const uint32_t i = (blk - rest * nex + (rest + (uint32_t)s) % nex) % nex;
+  int64_t len = length ? (int64_t)length[i] : T;
+  len = len < 0 ? 0 : (len > T ? T : len);
+  const int64_t t0 = (int64_t)c * CT;
+  const ProjTab md = tab[s];
+  if (t0 >= len) {  // uniform
+    if (!TOK && direct)
+      for (int e = threadIdx.x; e < KK; e += 256) dst[(int64_t)i * ldo + md.out_col + e] = 0.f;
+    return;
+  }
+  const int ntok = (int)(len - t0 < CT ? len - t0 : CT);
+  const int64_t row0 = (row_offset ? row_offset[i] : (int64_t)i * T) + t0;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const char* a_ptr = (const char*)md.a + row0 * md.lda * EB;
+  const char* g_ptr = (const char*)md.g + row0 * md.ldg * EB;
+  const uint32_t a_bytes = (uint32_t)(ntok * md.lda * EB), g_bytes = (uint32_t)(ntok * md.ldg * EB);
+  const uint32_t pk_side = (uint32_t)md.d_in * (uint32_t)(K * EB);  // packed S, then packed R
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(md.pk, pk_side + (uint32_t)md.d_out * (uint32_t)(K * EB));
+  // this wave's K-groups: [a0, a0 + na) of a, then [g0, g0 + n - na) of g
+  const int ga = md.d_in / KG, gg = md.d_out / KG;
+  const int a0 = ga * wave / 4, na = ga * (wave + 1) / 4 - a0;
+  const int g0 = gg * wave / 4, n = na + gg * (wave + 1) / 4 - g0;
+  const int lrow = lane >> 3, lch = lane & 7;
+  const uint32_t va = (uint32_t)((int64_t)lrow * md.lda * EB + lch * 16);
+  const uint32_t vg = (uint32_t)((int64_t)lrow * md.ldg * EB + lch * 16);
+  const uint32_t sa8 = (uint32_t)(8 * md.lda * EB), sg8 = (uint32_t)(8 * md.ldg * EB);
+  constexpr uint32_t kPast = 0xc0000000u;  // outside every descriptor's range
+
+  i32x4 xb[PD][TT][2], bb[PD][2][NK];
+  auto issue = [&](int j, i32x4 (&x)[TT][2], i32x4 (&b)[2][NK]) {
+    const bool on_a = j < na, live = j < n;
+    const int grp = on_a ? a0 + j : g0 + (j - na);
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(on_a ? a_ptr : g_ptr, on_a ? a_bytes : g_bytes);
+    const uint32_t off = live ? (on_a ? va : vg) + (uint32_t)grp * 128u : kPast;
+    const uint32_t s8 = live ? (on_a ? sa8 : sg8) : 0u;
+    const uint32_t boff = live ? (on_a ? 0u : pk_side) + (uint32_t)grp * (uint32_t)(2 * NK * 1024) + (uint32_t)lane * 16u
+                               : kPast;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int ct = 0; ct < NK; ++ct) b[h][ct] = load16_cached(rb, boff + (uint32_t)((h * NK + ct) * 1024));
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      x[tt][0] = load16_stream(r, off + (uint32_t)(2 * tt) * s8);
+      x[tt][1] = load16_stream(r, off + (uint32_t)(2 * tt + 1) * s8);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < PD; ++u) issue(u, xb[u], bb[u]);
+
+  // the transpose tile of project_side
+  i32x4* xp = sh + wave * XP;
+  const int wslot = lrow * 8 + (lch ^ lrow);
+  const int ri = lane & 15, rgrp = lane >> 4;
+  const int rslot0 = ri * 8 + (rgrp ^ (ri & 7));
+  const int rslot1 = ri * 8 + ((4 + rgrp) ^ (ri & 7));
+  const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 At[TT][NK], acc[TT][NK];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+    for (int ct = 0; ct < NK; ++ct) At[tt][ct] = acc[tt][ct] = zero4;
+  auto side_done = [&]() {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int ct = 0; ct < NK; ++ct) {
+        At[tt][ct] = acc[tt][ct];
+        acc[tt][ct] = zero4;
+      }
+  };
+  for (int j0 = 0; j0 < n; j0 += PD) {
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+      const int j = j0 + u;
+      if (j == na) side_done();
+      if (j < n) {
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          xp[tt * 128 + wslot] = xb[u][tt][0];
+          xp[tt * 128 + 64 + wslot] = xb[u][tt][1];
+        }
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          if (16 * tt >= ntok) break;  // tiles without tokens: uniform
+          const i32x4 f0 = xp[tt * 128 + rslot0];
+          const i32x4 f1 = xp[tt * 128 + rslot1];
+#pragma unroll
+          for (int ct = 0; ct < NK; ++ct) {
+            acc[tt][ct] = mma16(Tag{}, f0, bb[u][0][ct], acc[tt][ct]);
+            acc[tt][ct] = mma16(Tag{}, f1, bb[u][1][ct], acc[tt][ct]);
+          }
+        }
+      }
+      issue(j + PD, xb[u], bb[u]);
+    }
+  }
+  // na == n: the loop may have ended before it reached index na
+  if (na == n && n % PD == 0) side_done();
+
+  // every wave's tiles to LDS, [wave][tt][ct][q][lane], one side after the
+  // other; wave w adds the four waves' register w of every tile (tokens 16 tt +
+  // 4 (lane / 16) + w, column lane % 16) and contracts those tokens
+  float* ex = reinterpret_cast<float*>(sh);
+  auto exchange = [&](const f32x4 (&own)[TT][NK], float (&sum)[TT][NK]) {
+    __syncthreads();  // the buffer's last readers are done
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int ct = 0; ct < NK; ++ct)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ex[((wave * PT + tt * NK + ct) * 4 + q) * kWave + lane] = own[tt][ct][q];
+    __syncthreads();
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int ct = 0; ct < NK; ++ct) {
+        const float* e = ex + ((tt * NK + ct) * 4 + wave) * kWave + lane;
+        float v = e[0];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += e[w * PT * 4 * kWave];
+        sum[tt][ct] = v;
+      }
+  };
+  float aq[TT][NK], gq[TT][NK];
+  exchange(At, aq);
+  exchange(acc, gq);
+  if constexpr (TOK) {
+    // each 16-lane row writes its own token's block (as in project_item)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const int tw = 16 * tt + 4 * (lane >> 4) + wave;
+      if (tw < ntok && row0 + tw < n_rows) {  // whole 16-lane rows
+        float* orow = dst + (row0 + tw) * ldo + md.out_col + (lane & 15);
+        StaticFor<0, 16 * NK>::run([&](auto rc) {
+          constexpr int r = decltype(rc)::value;
+          const float gr = row_bcast<(r & 15)>(gq[tt][r >> 4]);
+#pragma unroll
+          for (int ct = 0; ct < NK; ++ct)
+            __builtin_nontemporal_store(gr * aq[tt][ct], orow + r * 16 * NK + 16 * ct);
+        });
+      }
+    }
+  } else {
+    f32x4 P[NK][NK];
+#pragma unroll
+    for (int rt = 0; rt < NK; ++rt)
+#pragma unroll
+      for (int ct = 0; ct < NK; ++ct) {
+        P[rt][ct] = zero4;
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+          P[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(gq[tt][rt], aq[tt][ct], P[rt][ct], 0, 0, 0);
+      }
+    __syncthreads();  // every wave has read the projected tiles
+    float* red = reinterpret_cast<float*>(sh);
+#pragma unroll
+    for (int rt = 0; rt < NK; ++rt)
+#pragma unroll
+      for (int ct = 0; ct < NK; ++ct)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave * KK + ((rt * NK + ct) * 4 + q) * kWave + lane] = P[rt][ct][q];
+    __syncthreads();
+    float* part = dst + (((int64_t)s * n_chunks + c) * n_ex + i) * KK;
+    float* orow = dst + (int64_t)i * ldo + md.out_col;
+    for (int e = threadIdx.x; e < KK; e += 256) {
+      const float v = ((red[e] + red[KK + e]) + red[2 * KK + e]) + red[3 * KK + e];
+      if (direct) {
+        orow[block_pos<NK>(e)] = v;
+      } else {
+        part[e] = v;
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // reduce: out[i, out_col + r*k + c] = sum over chunks of the item partials.
-// Partial element e = ((rt*NK + ct)*4 + q)*64 + lane holds
-// r = 16 rt + 4 (lane / 16) + q, c = 16 ct + lane % 16.
 // ---------------------------------------------------------------------------
 template <int NK>
 __global__ __launch_bounds__(256) void project_reduce_kernel(
     const ProjTab* __restrict__ tab, int n_chunks, int64_t n_ex, int64_t T, int CT,
     const int32_t* __restrict__ length, const float* __restrict__ partial,
     float* __restrict__ out, int64_t ldo) {
-  constexpr int K = 16 * NK;
-  constexpr int KK = K * K;
+  constexpr int KK = 256 * NK * NK;
   const int64_t i = blockIdx.x % n_ex;
   const int s = (int)(blockIdx.x / n_ex);
   int64_t len = length ? (int64_t)length[i] : T;
@@ -577,13 +810,7 @@ __global__ __launch_bounds__(256) void project_reduce_kernel(
   for (int e = threadIdx.x; e < KK; e += blockDim.x) {
     float v = 0.f;
     for (int c = 0; c < nck; ++c) v += partial[((((int64_t)s * n_chunks + c) * n_ex) + i) * KK + e];
-    const int lane = e & 63;
-    const int q = (e >> 6) & 3;
-    const int tile = e >> 8;
-    const int rt = tile / NK, ct = tile % NK;
-    const int r = 16 * rt + 4 * (lane >> 4) + q;
-    const int cc = 16 * ct + (lane & 15);
-    out[i * ldo + out_col + r * K + cc] = v;
+    out[i * ldo + out_col + block_pos<NK>(e)] = v;
   }
 }
 
@@ -608,7 +835,8 @@ hipError_t project_scratch(void** ptr) {
 }
 
 int project_chunk_tokens(int nk) {
-  return 64 * (nk == 1 ? ATTR_PROJ_TT1 : (nk == 2 ? 2 : 1));
+  (void)nk;
+  return 64 * Tiles<1>::TT;  // the same for every width
 }
 
 size_t project_packed_bytes(int64_t d_in, int64_t d_out, int k, int elem_bytes) {
@@ -669,12 +897,92 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
   return hipGetLastError();
 }
 
-hipError_t launch_project_reduce(int nk, const ProjTab* tab, int n_slots, int n_chunks,
+// Rates of the two kernels in elements of token rows (a and g widths times
+// tokens) per us and CU, and the latency of the longest item's K-groups that
+// the split saves, in us per group; from 12-layer GPT-2-shaped and 2- to
+// 6-layer 1B-shaped calls of 16 to 16384 tokens, even and ragged.
+struct FewRates {
+  double general, few, group;
+};
+static FewRates few_rates(bool bf16, int nk) {
+  if (bf16) return nk == 1 ? FewRates{14000, 12800, 0.3} : nk == 2 ? FewRates{12000, 11250, 0.15} : FewRates{10500, 8000, 0.08};
+  return FewRates{7000, 6700, 0.3};
+}
+
+// The general kernel reads a once per group and runs a little faster where
+// there are items enough; the split one has a chain a quarter as long and
+// wastes at most 63 tokens of a chunk.  Both times are modelled and the lower
+// one is taken.  fp32 at k = 32 and 64 is bound by the matrix cores and always
+// takes the split kernel, which computes no tile without tokens (16 ragged
+// GPT-2-shaped examples of up to 512 tokens: 682 -> 609 us at k = 32, 1224 ->
+// 926 at k = 64; 16384 tokens: 1916 -> 1752 and 3552 -> 2796).  bf16, k = 16,
+// 12 GPT-2-shaped layers, general / split: one example of 16 tokens 46 / 16
+// us, 389 tokens 86 / 46, 1024 tokens 99 / 75, 8 x 512 tokens 228 / 209, 16 x
+// 512 397 / 392, 32 x 512 743 / 759; 2 1B-shaped layers: 149 tokens 229 / 29,
+// 4 x 1343 297 / 187, 8 x 2048 506 / 538.
+ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64_t slot_cost, int64_t longest,
+                             int64_t n_slots, int64_t n_ex, int64_t T, bool ragged) {
+  ProjFewPlan P{};
+  constexpr int64_t kCus = 256;
+  const int64_t ct = project_chunk_tokens(nk);
+  if (bf16 || nk == 1) {
+    // tokens an example costs; of ragged ones about 0.56 T are valid (lengths
+    // even over T / 8 .. T), with half a chunk lost at the end.  At k = 16 a
+    // chunk's tokens are spread over the waves and only the loads cost.
+    const double valid = ragged ? 0.56 * (double)T : (double)T;
+    auto cost_tokens = [&](int64_t c) {
+      if (nk == 1) return valid + 32.0;
+      return ragged && T > c ? valid + 0.5 * (double)c : (double)((T + c - 1) / c * c);
+    };
+    const FewRates r = few_rates(bf16, nk);
+    const double tg = (double)group_cost * cost_tokens(ct) * (double)n_ex / (double)kCus / r.general;
+    const double tf = (double)slot_cost * cost_tokens(64) * (double)n_ex / (double)kCus / r.few;
+    const double groups = (double)longest * (bf16 ? 2 : 4) / 128.0;
+    if (!(tf < tg + r.group * groups)) return P;
+  }
+  // One token tile per workgroup where even then few workgroups exist and the
+  // modules are wide: R and S are read four times as often (one 149-token
+  // example of 2 1B-shaped layers: 40 -> 29 us; of 128 tokens over 12
+  // GPT-2-shaped layers: 28 -> 32 us).
+  const int tt = n_slots * ((T + 15) / 16) * n_ex * 24 <= slot_cost / n_slots ? 1 : 4;
+  const int64_t chunks = (T + 16 * tt - 1) / (16 * tt);
+  if (n_slots * chunks * n_ex > ((int64_t)1 << 24)) return P;
+  P.ct = 16 * tt;
+  P.n_chunks = (int)chunks;
+  return P;
+}
+
+hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, const ProjTab* tab, int n_slots,
+                              int64_t n_ex, int64_t T, const int64_t* row_offset, const int32_t* length,
+                              float* dst, bool tok, int64_t ldo, int64_t n_rows, hipStream_t s) {
+  dim3 grid((unsigned)((int64_t)n_slots * P.n_chunks * n_ex)), block(256);
+  const int direct = !tok && P.n_chunks == 1;
+#define ATTR_FEW(B, N, TT)                                                                            \
+  if (nk == N && P.ct == 16 * TT) {                                                                   \
+    if (tok)                                                                                          \
+      hipLaunchKernelGGL((project_few_kernel<B, N, TT, true>), grid, block, 0, s, tab, P.n_chunks, n_ex, \
+                         T, row_offset, length, dst, ldo, n_rows, direct);                            \
+    else                                                                                              \
+      hipLaunchKernelGGL((project_few_kernel<B, N, TT, false>), grid, block, 0, s, tab, P.n_chunks, n_ex, \
+                         T, row_offset, length, dst, ldo, n_rows, direct);                            \
+  }
+#define ATTR_FEW_NK(B) \
+  ATTR_FEW(B, 1, 4) ATTR_FEW(B, 1, 1) ATTR_FEW(B, 2, 4) ATTR_FEW(B, 2, 1) ATTR_FEW(B, 4, 4) ATTR_FEW(B, 4, 1)
+  if (bf16) {
+    ATTR_FEW_NK(true)
+  } else {
+    ATTR_FEW_NK(false)
+  }
+#undef ATTR_FEW_NK
+#undef ATTR_FEW
+  return hipGetLastError();
+}
+
+hipError_t launch_project_reduce(int nk, int CT, const ProjTab* tab, int n_slots, int n_chunks,
                                  int64_t n_ex, int64_t T, const int32_t* length,
                                  const float* partial, float* out, int64_t ldo,
                                  hipStream_t s) {
   dim3 grid((unsigned)((int64_t)n_slots * n_ex)), block(256);
-  const int CT = project_chunk_tokens(nk);
 #define ATTR_RED(N)                                                                          \
   hipLaunchKernelGGL((project_reduce_kernel<N>), grid, block, 0, s, tab, n_chunks, n_ex, T, CT, \
                      length, partial, out, ldo)
