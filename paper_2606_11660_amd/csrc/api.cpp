@@ -60,6 +60,9 @@ bool overlap(Span a, Span b) { return a.lo < b.hi && b.lo < a.hi; }
 // ---------------------------------------------------------------------------
 struct ProjLayout {
   size_t off_tab, off_gtab, off_wl, off_pk, off_part, total;
+  attr::ProjFewPlan few;  // ct = 0: the general kernel
+  size_t few_total;       // bytes of the few-item plan (its partials at off_part)
+  size_t query;           // bytes that the workspace query returns
   std::vector<int> order;       // slot -> module index
   std::vector<size_t> pk_off;   // per slot, relative to off_pk
   std::vector<int> slot_grp;    // slot -> group
@@ -69,7 +72,7 @@ struct ProjLayout {
 };
 
 ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64_t n_ex,
-                          int64_t T, int k, bool tok = false) {
+                          int64_t T, int k, bool tok = false, bool ragged = false) {
   ProjLayout L;
   const int nk = k / 16;
   // Modules that read the same input rows (same a, lda and d_in: q/k/v or
@@ -138,6 +141,19 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   // group table fits what the query (which does not know the call) returns
   if (!tok) off += align_up((size_t)n_mods * (size_t)L.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
   L.total = off;
+  int64_t group_cost = 0, slot_cost = 0;
+  for (const auto& gm : groups) group_cost += cost(gm);
+  for (int x = 0; x < n_mods; ++x) slot_cost += mods[x].d_in + mods[x].d_out;
+  // the plan of this call, and the bytes of the larger of the plans with and
+  // without lengths: the query does not know which the call will have
+  L.query = L.total;
+  for (const bool r : {!ragged, ragged}) {
+    L.few = attr::plan_project_few(eb == 2, nk, group_cost, slot_cost, cost(groups[0]), n_mods, n_ex, T, r);
+    L.few_total = L.off_part;
+    if (L.few.ct && L.few.n_chunks > 1 && !tok)
+      L.few_total += align_up((size_t)n_mods * (size_t)L.few.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
+    L.query = std::max(L.query, L.few_total);
+  }
   return L;
 }
 
@@ -221,7 +237,7 @@ size_t attr_project_workspace_size(const attr_module* mods, int32_t n_mods, attr
     if (!mods || n_mods < 1 || n_mods > 4096 || (k != 16 && k != 32 && k != 64) || T < 1 ||
         n_examples < 0 || (in_dtype != ATTR_BF16 && in_dtype != ATTR_F32))
       return 0;
-    return project_layout(mods, n_mods, dtype_bytes(in_dtype), n_examples, T, k).total;
+    return project_layout(mods, n_mods, dtype_bytes(in_dtype), n_examples, T, k).query;
   } catch (...) {
     return 0;
   }
@@ -241,7 +257,7 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
     if (tok && n_rows < 0) return fail(ATTR_ERR_INVALID_ARG, "n_rows=%lld is negative", (long long)n_rows);
     if (n_examples == 0) return ATTR_OK;
     const int eb = dtype_bytes(in_dtype);
-    ProjLayout L = project_layout(mods, n_mods, eb, n_examples, T, k, tok);
+    ProjLayout L = project_layout(mods, n_mods, eb, n_examples, T, k, tok, length != nullptr);
     if (!ws || ws_bytes < L.total)
       return fail(ATTR_ERR_WORKSPACE, "attr_project needs %zu workspace bytes, got %zu", L.total,
                   ws ? ws_bytes : (size_t)0);
@@ -285,19 +301,31 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
       hipError_t e = attr::launch_project_pack(bf16, nk, pa, tab, gtab, pk, s);
       if (e != hipSuccess) return device_fail(e, "attr_project pack launch");
     }
-    int32_t* wl_perm = nullptr;
-    int32_t* wl_off = nullptr;
-    if (attr::project_uses_worklist(length, n_examples, L.n_chunks)) {
-      wl_perm = reinterpret_cast<int32_t*>(base + L.off_wl);
-      wl_off = reinterpret_cast<int32_t*>(base + L.off_wl + align_up(4 * (size_t)n_examples));
+    hipError_t e;
+    int n_chunks = L.n_chunks, ct = attr::project_chunk_tokens(nk);
+    bool reduce = !tok;
+    // a workspace sized for the general path alone takes the general path
+    if (L.few.ct && ws_bytes >= L.few_total) {
+      n_chunks = L.few.n_chunks;
+      ct = L.few.ct;
+      reduce = !tok && n_chunks > 1;
+      e = attr::launch_project_few(bf16, nk, L.few, tab, n_mods, n_examples, T, row_offset, length,
+                                   reduce ? part : out, tok, ldo, n_rows, s);
+    } else {
+      int32_t* wl_perm = nullptr;
+      int32_t* wl_off = nullptr;
+      if (attr::project_uses_worklist(length, n_examples, L.n_chunks)) {
+        wl_perm = reinterpret_cast<int32_t*>(base + L.off_wl);
+        wl_off = reinterpret_cast<int32_t*>(base + L.off_wl + align_up(4 * (size_t)n_examples));
+      }
+      e = attr::launch_project_main(bf16, nk, tab, gtab, L.n_groups, L.n_chunks, n_examples, T,
+                                    row_offset, length, wl_perm, wl_off, tok ? out : part, s, tok, ldo,
+                                    n_rows);
     }
-    hipError_t e = attr::launch_project_main(bf16, nk, tab, gtab, L.n_groups, L.n_chunks,
-                                             n_examples, T, row_offset, length, wl_perm, wl_off,
-                                             tok ? out : part, s, tok, ldo, n_rows);
     if (e != hipSuccess) return device_fail(e, "attr_project main launch");
-    if (tok) return ATTR_OK;
-    e = attr::launch_project_reduce(nk, tab, n_mods, L.n_chunks, n_examples, T, length, part, out,
-                                    ldo, s);
+    if (!reduce) return ATTR_OK;
+    e = attr::launch_project_reduce(nk, ct, tab, n_mods, n_chunks, n_examples, T, length, part, out, ldo,
+                                    s);
     if (e != hipSuccess) return device_fail(e, "attr_project reduce launch");
     return ATTR_OK;
   } catch (const std::exception& ex) {
