@@ -110,6 +110,23 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+_native_modules = None
+
+
+def _native():
+    """The native gatherer of module descriptors (csrc/marshal.cpp), loaded once;
+    raises if it has not been built."""
+    global _native_modules
+    if _native_modules is None:
+        try:
+            from ._marshal import modules
+        except ModuleNotFoundError as e:
+            raise ImportError("_marshal.so is missing: build it with "
+                              "`python -m paper_2606_11660_amd.build`") from e
+        _native_modules = modules
+    return _native_modules
+
+
 def _check(status: int) -> None:
     if status != 0:
         raise AttrError(status, lib().attr_last_error().decode(errors="replace"))
@@ -123,6 +140,11 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _call_stream(stream):
+    """The call's stream, looked up once."""
+    return torch.cuda.current_stream() if stream is None else stream
 
 
 def _dtype(t: torch.Tensor) -> int:
@@ -152,7 +174,7 @@ def _same_gpu(*tensors: Optional[torch.Tensor]) -> None:
         return
     d = ts[0].device
     for t in ts:
-        if t.device.type != "cuda" or t.device != d:
+        if not t.is_cuda or t.device != d:
             raise ValueError("every tensor must live on the same GPU device")
 
 
@@ -177,10 +199,15 @@ class Workspace:
 
     A workspace serves one stream at a time: calls that may overlap on
     different streams need workspaces of their own (the default workspace is
-    kept per device and stream).  Every use records its stream on the
-    buffer, so a buffer replaced by a larger one is not handed out again by
-    torch's allocator before the work queued on those streams has finished.
+    kept per device and stream).  Every stream of use is recorded on the
+    buffer (once: torch's allocator keeps a buffer's streams until it is
+    freed), so a buffer replaced by a larger one is not handed out again
+    before the work queued on those streams has finished.
     """
+
+    # the buffer whose streams of use have been recorded, and those streams
+    _recorded_on: Optional[torch.Tensor] = None
+    _recorded: set = set()
 
     def __init__(self, device=None):
         self.device = torch.device(device or "cuda")
@@ -191,17 +218,22 @@ class Workspace:
             return None, 0
         if self.buf is None or self.buf.numel() < nbytes:
             self.buf = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
-        self.buf.record_stream(_torch_stream(stream))
+        if self._recorded_on is not self.buf:
+            self._recorded_on, self._recorded = self.buf, set()
+        raw = _stream(stream)
+        if raw not in self._recorded:
+            self.buf.record_stream(_torch_stream(stream))
+            self._recorded.add(raw)
         return self.buf.data_ptr(), self.buf.numel()
 
 
-_default_ws: Dict[Tuple[str, int], Workspace] = {}
+_default_ws: Dict[Tuple[torch.device, int], Workspace] = {}
 
 
 def _ws(ws: Optional[Workspace], device, stream=None) -> Workspace:
     if ws is not None:
         return ws
-    key = (str(device), _stream(stream))
+    key = (device, _stream(stream))
     if key not in _default_ws:
         _default_ws[key] = Workspace(device)
     return _default_ws[key]
@@ -283,6 +315,16 @@ def _check_modules(mods: Sequence[Module], k: int, n_examples: int, T: int,
     return _dtype(mods[0].a)
 
 
+def _project_args(mods: Sequence[Module], k: int, n_examples: int, T: int,
+                  row_offset: Optional[torch.Tensor], length: Optional[torch.Tensor], out: torch.Tensor,
+                  out_rows_needed: int):
+    """(dtype code, module descriptors) of a checked projection call."""
+    got = _native()(mods, Module, k, n_examples, T, row_offset, length, out, out_rows_needed)
+    if got is not None:
+        return got[0], (_CModule * len(mods)).from_buffer(got[1])
+    return _check_modules(mods, k, n_examples, T, row_offset, length, out, out_rows_needed), _cmods(mods)
+
+
 def attr_project_workspace_size(mods: Sequence[Module], in_dtype: int, n_examples: int, T: int,
                                 k: int) -> int:
     return int(lib().attr_project_workspace_size(_cmods(mods), len(mods), in_dtype, n_examples, T, k))
@@ -299,9 +341,9 @@ def attr_project(mods: Sequence[Module], k: int, n_examples: int, T: int,
     and the caller keeps every valid token inside a and g (device values
     cannot be checked here).  length: int32 [n_examples] on the device,
     clamped to [0, T] by the library."""
-    in_dtype = _check_modules(mods, k, n_examples, T, row_offset, length, out, n_examples)
-    cm = _cmods(mods)
+    in_dtype, cm = _project_args(mods, k, n_examples, T, row_offset, length, out, n_examples)
     L = lib()
+    stream = _call_stream(stream)
     need = L.attr_project_workspace_size(cm, len(mods), in_dtype, n_examples, T, k)
     wsp, wsn = _ws(ws, out.device, stream).get(need, stream)
     _check(L.attr_project(cm, len(mods), in_dtype, k, n_examples, T, _ptr(row_offset), _ptr(length),
@@ -316,8 +358,8 @@ def attr_project_noalloc(mods: Sequence[Module], k: int, n_examples: int, T: int
     (ATTR_PROJECT_NOALLOC_SCRATCH bytes) serves as workspace, so this call
     allocates nothing (usable under graph capture).  Calls that overlap on one
     GPU share that scratch and must be ordered by the caller."""
-    in_dtype = _check_modules(mods, k, n_examples, T, row_offset, length, out, n_examples)
-    _check(lib().attr_project_noalloc(_cmods(mods), len(mods), in_dtype, k, n_examples, T,
+    in_dtype, cm = _project_args(mods, k, n_examples, T, row_offset, length, out, n_examples)
+    _check(lib().attr_project_noalloc(cm, len(mods), in_dtype, k, n_examples, T,
                                       _ptr(row_offset), _ptr(length), out.data_ptr(),
                                       out.stride(0), _stream(stream)))
     return out
@@ -329,9 +371,9 @@ def attr_project_tokens(mods: Sequence[Module], k: int, n_examples: int, T: int,
                         stream=None) -> torch.Tensor:
     """Per-token blocks (R^T g_t)(S^T a_t)^T into out[token row, out_col:out_col+k*k];
     rows at or past out.shape[0] are not written."""
-    in_dtype = _check_modules(mods, k, n_examples, T, row_offset, length, out, 0)
-    cm = _cmods(mods)
+    in_dtype, cm = _project_args(mods, k, n_examples, T, row_offset, length, out, 0)
     L = lib()
+    stream = _call_stream(stream)
     need = L.attr_project_workspace_size(cm, len(mods), in_dtype, n_examples, T, k)
     wsp, wsn = _ws(ws, out.device, stream).get(need, stream)
     _check(L.attr_project_tokens(cm, len(mods), in_dtype, k, n_examples, T, _ptr(row_offset),
@@ -370,6 +412,7 @@ def attr_precond_accumulate(X: torch.Tensor, mode: int, H: torch.Tensor,
     _check_precond_matrix(H, mode, D, "H")
     _same_gpu(X, H)
     L = lib()
+    stream = _call_stream(stream)
     need = L.attr_precond_accumulate_workspace_size(n, D, xd, mode)
     wsp, wsn = _ws(ws, X.device, stream).get(need, stream)
     _check(L.attr_precond_accumulate(X.data_ptr(), xd, n, D, ldx, mode, H.data_ptr(), wsp, wsn,
@@ -391,6 +434,7 @@ def attr_precond_apply(X: torch.Tensor, mode: int, M: Optional[torch.Tensor], un
     _check_precond_matrix(M, mode, D, "M")
     _same_gpu(X, Y, M)
     L = lib()
+    stream = _call_stream(stream)
     need = L.attr_precond_apply_workspace_size(n, D, mode)
     wsp, wsn = _ws(ws, X.device, stream).get(need, stream)
     _check(L.attr_precond_apply(X.data_ptr(), _dtype(X), n, D, ldx, mode, _ptr(M),
@@ -424,6 +468,7 @@ def attr_score_topk(Q: torch.Tensor, G: torch.Tensor, k: int, top_score: torch.T
         raise ValueError(f"top_score and top_index must be [{nq}, {k}]")
     _same_gpu(Q, G, top_score, top_index)
     L = lib()
+    stream = _call_stream(stream)
     need = L.attr_score_topk_workspace_size(nq, ng, D, k)
     wsp, wsn = _ws(ws, Q.device, stream).get(need, stream)
     _check(L.attr_score_topk(Q.data_ptr(), nq, ldq, G.data_ptr(), ng, ldg, _dtype(Q), D, k,

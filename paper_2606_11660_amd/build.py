@@ -25,6 +25,8 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIP_SOURCES = ["project.hip", "rowwise.hip", "syrk.hip", "apply_full.hip", "apply_few.hip",
                "score.hip", "probe.hip"]
 CXX_SOURCES = ["api.cpp"]
+# the Python binding's native part (torch's and Python's headers, no device code)
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", f"-I{INCLUDE}", f"-I{CSRC}", "-Wall",
           "-Wno-unused-function"]
@@ -216,6 +218,22 @@ def asm_valu_mfma_hazards(asm: str, need: int = 2) -> list:
     return sorted(set(found))
 
 
+def _marshal_command(out: str) -> list:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    gxx = shutil.which("g++")
+    if gxx is None:
+        raise RuntimeError("g++ not found")
+    inc = [f"-isystem{p}" for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [gxx, "-O2", "-fPIC", "-shared", "-std=c++17", "-Wall", f"-I{INCLUDE}", *inc,
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            os.path.join(CSRC, "marshal.cpp"), f"-L{libdir}", "-ltorch_python", "-ltorch_cpu", "-lc10",
+            "-o", out]
+
+
 def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
     os.makedirs(BUILD, exist_ok=True)
@@ -231,6 +249,8 @@ def build(verbose: bool = False) -> str:
         jobs.append([hipcc, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__",
                      f"-I{ROCM}/include", "-c", os.path.join(CSRC, src), "-o", obj])
     objs = [j[-1] for j in jobs]
+    marshal_tmp = MARSHAL + ".tmp"
+    marshal_job = _marshal_command(marshal_tmp)
     # device assembly of every HIP source, checked for unprotected loads
     asm_jobs = []
     for src in HIP_SOURCES:
@@ -239,7 +259,7 @@ def build(verbose: bool = False) -> str:
             asm_jobs.append([hipcc, *COMMON, *DEVICE, "--cuda-device-only", "-S", "-x", "hip", path,
                              "-o", os.path.join(BUILD, src + ".s")])
     with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs) + len(asm_jobs))) as ex:
-        for out in ex.map(_run, jobs + asm_jobs):
+        for out in ex.map(_run, [marshal_job] + jobs + asm_jobs):
             if verbose and out.strip():
                 print(out)
     hazards = []
@@ -252,6 +272,7 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     _run([hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
+    os.replace(marshal_tmp, MARSHAL)
     return LIB
 
 
