@@ -16,11 +16,11 @@
 //    of rows into the workspace and an exact selection kernel reads them.
 //  * split-K (small stores, too few tiles to fill 256 CUs): workgroups own
 //    (tile, D-slice) pairs and write fp32 partial scores; one workgroup per
-//    query and part of the rows sums the slices in slice order and selects
-//    by a threshold from 16-row segment maxima and a sort.
-// Either way, per-partition sorted lists are merged per query by block-wide
-// arg-max in (score desc, index asc) order, which also merges a previous
-// result when a store is scored chunk by chunk.
+//    query sums the slices in slice order and selects by a threshold from
+//    its threads' best rows and a sort.
+// Where rows are partitioned, the sorted lists are merged per query by a
+// threshold and a sort in (score desc, index asc) order, which also merges a
+// previous result when a store is scored chunk by chunk.
 #include "common.h"
 #include "gemm.h"
 #include "kernels.h"
@@ -30,7 +30,7 @@ namespace {
 
 constexpr int SQB = 64;       // queries per workgroup
 constexpr int STN = 128;      // store rows per tile (4 waves x 32 rows)
-constexpr int SPD = 3;        // 128-byte K-groups of store loads in flight (5 or 7: no faster)
+constexpr int SPD = 3;        // 128-byte K-groups of store loads in flight (up to 12: no faster)
 
 template <bool F16>
 struct STag;
@@ -48,11 +48,15 @@ struct STag<false> {
 // acc[qt][rt] (+)= Q[16 qt + i, groups) . G[32 wave + 16 rt + j, groups) for
 // the K-groups [g_begin, g_end).  Lane layout of acc: query 16 qt + 4 (lane
 // / 16) + r (register r), row 16 rt + lane % 16.
-template <bool F16>
+// QT: 16-query tiles of the block (1, 2 or 4): a block of few queries issues no
+// products and no loads for the others (10 queries x 11335 rows x 6528 in fp16
+// 64 -> 51 us a call, 15 x 6161 x 3840 in fp32, where the products count, 64 ->
+// 40 us).
+template <bool F16, int QT>
 __device__ inline void score_tile(__amdgpu_buffer_rsrc_t rq, int64_t ldq,
                                   __amdgpu_buffer_rsrc_t rg, int64_t ldg, int g_begin,
                                   int g_end, int lane, i32x4* __restrict__ xp,
-                                  f32x4 (&acc)[4][2]) {
+                                  f32x4 (&acc)[QT][2]) {
   using Tag = typename STag<F16>::tag;
   constexpr int EB = STag<F16>::bytes;
   constexpr int E = 16 / EB;
@@ -68,7 +72,7 @@ __device__ inline void score_tile(__amdgpu_buffer_rsrc_t rq, int64_t ldq,
   const uint32_t q_base = (uint32_t)(((int64_t)ri * ldq + E * rgrp) * EB);
   const uint32_t q_tile = (uint32_t)(16 * ldq * EB);
 
-  i32x4 gbuf[SPD][2][2], qcur[2][4], qnxt[2][4];
+  i32x4 gbuf[SPD][2][2], qcur[2][QT], qnxt[2][QT];
   auto issue_g = [&](int grp, i32x4 (&gb)[2][2]) {
     const uint32_t off = g_base + (uint32_t)grp * 128u;
 #pragma unroll
@@ -77,11 +81,11 @@ __device__ inline void score_tile(__amdgpu_buffer_rsrc_t rq, int64_t ldq,
       gb[rt][1] = load16_stream(rg, off + rt * g_tile + g_half);
     }
   };
-  auto issue_q = [&](int grp, i32x4 (&qf)[2][4]) {
+  auto issue_q = [&](int grp, i32x4 (&qf)[2][QT]) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int qt = 0; qt < 4; ++qt)
+      for (int qt = 0; qt < QT; ++qt)
         qf[s][qt] = load16_cached(rq, q_base + qt * q_tile + (uint32_t)((2 * grp + s) * KS * EB));
   };
 #pragma unroll
@@ -106,7 +110,7 @@ __device__ inline void score_tile(__amdgpu_buffer_rsrc_t rq, int64_t ldq,
           const i32x4 f0 = xp[rt * 128 + rslot0];
           const i32x4 f1 = xp[rt * 128 + rslot1];
 #pragma unroll
-          for (int qt = 0; qt < 4; ++qt) {
+          for (int qt = 0; qt < QT; ++qt) {
             acc[qt][rt] = mma16(Tag{}, qcur[0][qt], f0, acc[qt][rt]);
             acc[qt][rt] = mma16(Tag{}, qcur[1][qt], f1, acc[qt][rt]);
           }
@@ -114,7 +118,7 @@ __device__ inline void score_tile(__amdgpu_buffer_rsrc_t rq, int64_t ldq,
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-          for (int qt = 0; qt < 4; ++qt) qcur[s][qt] = qnxt[s][qt];
+          for (int qt = 0; qt < QT; ++qt) qcur[s][qt] = qnxt[s][qt];
       }
     }
   }
@@ -657,6 +661,45 @@ __device__ inline uint64_t rs_key(uint32_t key, int64_t j) {
   return ((uint64_t)key << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
 }
 
+// A threshold at or below the k-th largest of the block's keys (V per thread, 0
+// = none) that at least k keys reach: exactly that key, or, with slack, the
+// first threshold found that at most k + slack keys reach.  0 when fewer than k
+// keys are there.  Two bits a step from the top, counted by ballots: 16 steps of
+// one barrier each, where a bitonic sort of 1024 keys takes 55 (k-th of the 256
+// prefix maxima of a query: 21 -> 5 us).  cnt: 48 counters in LDS.
+template <int NT, int V>
+__device__ inline uint32_t block_kth(const uint32_t (&key)[V], int k, int slack, int* cnt) {
+  const int t = threadIdx.x;
+  __syncthreads();  // the counters' last readers are done
+  if (t < 48) cnt[t] = 0;
+  __syncthreads();
+  uint32_t T = 0u;
+  for (int it = 0; it < 16; ++it) {
+    const int sh = 30 - 2 * it;
+    int n[3] = {0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+      for (uint32_t b = 1; b <= 3; ++b)
+        n[b - 1] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[v] >= (T | (b << sh))));
+    if ((t & 63) == 0) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        if (n[b]) atomicAdd(&cnt[3 * it + b], n[b]);
+    }
+    __syncthreads();
+    int have = 0;
+#pragma unroll
+    for (int b = 2; b >= 0; --b)
+      if (have == 0 && cnt[3 * it + b] >= k) {
+        have = cnt[3 * it + b];
+        T |= (uint32_t)(b + 1) << sh;
+      }
+    if (slack && have && have <= k + slack) break;  // uniform
+  }
+  return T;
+}
+
 // Descending bitonic sort of n (a power of two) keys in LDS, 256 threads.
 template <typename T>
 __device__ inline void bitonic_desc(T* a, int n) {
@@ -699,7 +742,8 @@ __global__ __launch_bounds__(256) void score_rselect_kernel(
     float* __restrict__ thr, int64_t nc, int k, int part, int n_parts, int64_t index_base,
     float* __restrict__ part_s, int64_t* __restrict__ part_i) {
   __shared__ uint64_t cand[RS_CAP];
-  __shared__ uint32_t smp[RS_MAXSEG];  // segment maxima or samples, sorted
+  __shared__ uint32_t smp[RS_SMP];  // samples, sorted
+  __shared__ int kcnt[48];
   __shared__ uint16_t segs[RS_MAXSEG];
   __shared__ uint64_t red_u[4];
   __shared__ int n_cand, n_pass;
@@ -781,14 +825,15 @@ __global__ __launch_bounds__(256) void score_rselect_kernel(
     // No bound yet: the k-th largest segment maximum.  k segments reach it,
     // so at least k scores do; unless one segment holds many of the top
     // scores, few more than k do.
-    int n_sort = 64;
-    while (n_sort < n_sc) n_sort <<= 1;
-    for (int g = t; g < n_sort; g += 256) {
-      const uint32_t key = g < n_sc ? fkey(sm[g]) : 0u;
-      smp[g] = selectable(key) ? key : 0u;
+    uint32_t key[RS_MAXSEG / 256];
+#pragma unroll
+    for (int u = 0; u < RS_MAXSEG / 256; ++u) {
+      const int g = t + 256 * u;
+      const uint32_t x = g < n_sc ? fkey(sm[g]) : 0u;
+      key[u] = selectable(x) ? x : 0u;
     }
-    bitonic_desc(smp, n_sort);
-    const uint32_t tau = k <= n_sc && smp[k - 1] ? smp[k - 1] : floor_key;
+    const uint32_t kth = block_kth<256>(key, k, 0, kcnt);
+    const uint32_t tau = kth ? kth : floor_key;
     c = collect(tau);
     ok = c <= RS_CAP;
   }
@@ -871,7 +916,7 @@ __global__ __launch_bounds__(256) void score_rselect_kernel(
 // ---------------------------------------------------------------------------
 // Partial scores of (query block, row tile, D-slice) -> spart[slice][q][row]
 // (nqp = 64 n_qb query rows of n_g scores per slice).
-template <bool F16>
+template <bool F16, int QT>
 __global__ __launch_bounds__(256) void score_splitk_kernel(
     const char* __restrict__ Q, int64_t n_q, int64_t ldq, const char* __restrict__ G,
     int64_t n_g, int64_t ldg, int n_grp, int n_qb, int n_tiles, int n_split,
@@ -896,22 +941,22 @@ __global__ __launch_bounds__(256) void score_splitk_kernel(
   int64_t nrow = n_g - r0;
   nrow = nrow < 0 ? 0 : (nrow > 32 ? 32 : nrow);
   const __amdgpu_buffer_rsrc_t rg = make_rsrc(G + r0 * ldg * EB, (uint32_t)(nrow * ldg * EB));
-  f32x4 acc[4][2];
+  f32x4 acc[QT][2];
 #pragma unroll
-  for (int qt = 0; qt < 4; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) acc[qt][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  score_tile<F16>(rq, ldq, rg, ldg, g_begin, g_end, lane, &xpose[wave][0], acc);
+  score_tile<F16, QT>(rq, ldq, rg, ldg, g_begin, g_end, lane, &xpose[wave][0], acc);
   float* dst = spart + (int64_t)split * n_g * nqp;
 #pragma unroll
-  for (int qt = 0; qt < 4; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t q = q0 + 16 * qt + 4 * (lane >> 4) + r;
         const int64_t row = r0 + 16 * rt + (lane & 15);
-        if (row < n_g) dst[q * n_g + row] = acc[qt][rt][r];
+        if (row < n_g && q < n_q) dst[q * n_g + row] = acc[qt][rt][r];
       }
 }
 
@@ -942,7 +987,7 @@ __device__ inline Cand wave_best(Cand c) {
   return c;
 }
 
-// One workgroup per query: k rounds of block arg-max over the source heads.
+
 // Split-K plan with at most 256 store rows (a batch of new rows scored and
 // merged into a running list): one wave per query sums the slices of its
 // scores in slice order and takes the k best of those rows and of the
@@ -1009,18 +1054,16 @@ __global__ __launch_bounds__(64) void score_small_select_kernel(
   }
 }
 
-// Up to 4 sources per thread: n_parts + merge <= 1024.
-constexpr int MERGE_SPT = 4;
-constexpr int MERGE_CAP = 2048;  // entries gathered and sorted in LDS
-constexpr int MERGE_ROUNDS_K = 24;  // k up to this: k arg-max rounds are faster than the sorts
+constexpr int SEL_NT = 1024;    // threads of the selection kernels below
+constexpr int SEL_CAP = 2048;   // entries gathered and sorted in LDS
 
-// Bitonic sort of n (a power of two, <= MERGE_CAP) candidates, best first
+// Bitonic sort of n (a power of two, <= SEL_CAP) candidates, best first
 // ((score desc, index asc), empty entries last).
 __device__ inline void bitonic_cand(Cand* a, int n) {
   for (int size = 2; size <= n; size <<= 1)
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
       __syncthreads();
-      for (int t = threadIdx.x; t < n / 2; t += 256) {
+      for (int t = threadIdx.x; t < n / 2; t += SEL_NT) {
         const int i = 2 * t - (t & (stride - 1));
         const int j = i + stride;
         const Cand x = a[i], y = a[j];
@@ -1033,283 +1076,209 @@ __device__ inline void bitonic_cand(Cand* a, int n) {
   __syncthreads();
 }
 
-// Split-K plan with more than 256 rows (a store of fewer than 32768 rows):
-// one workgroup per (query, part of at most 8192 rows).  Pass 1 sums every
-// row's slices (slice order, 32 loads in flight per thread) into LDS and
-// keeps the best row of each 16-row segment; tau, the k-th best of those
-// maxima, is reached by k distinct rows, so the k best of the part are at
-// or above it (with fewer than k segments every row qualifies).  Pass 2
-// gathers the rows at or above tau, and the previous list when merging
-// into a single part, into LDS; a bitonic sort orders them and the first k
-// are the part's list (random stores: ~1-2 k rows): the answer itself for a
-// single part, else a partition list for the merge kernel.  Should more
-// than SPL_CAP rows qualify (massive ties) the list is built by k rounds of
-// block arg-max instead.
-constexpr int SPL_SEG = 16;
-constexpr int SPL_CAP = MERGE_CAP - 128;  // gathered rows (the previous list takes <= 128 more)
-constexpr int SPL_PART = 8192;            // rows per part: their scores stay in LDS
-constexpr int SPL_SLD = 8;                // slices loaded at once
-
-__global__ __launch_bounds__(256) void score_split_topk_kernel(
-    const float* __restrict__ spart, int64_t nqp, int64_t n_g, int n_split, int k, int merge,
-    int64_t index_base, int n_parts, float* __restrict__ part_s, int64_t* __restrict__ part_i,
-    float* top_s, int64_t* top_i) {
-  __shared__ Cand buf[MERGE_CAP];  // segment maxima, then candidates, then (fallback) the list
-  __shared__ float sc[SPL_PART];
-  __shared__ Cand wbest[4];
-  __shared__ int cnt;
-  const int64_t q = blockIdx.x / (uint32_t)n_parts;
-  const int p = (int)(blockIdx.x % (uint32_t)n_parts);
-  const int t = threadIdx.x;
-  const int64_t r0 = (int64_t)p * SPL_PART;
-  int64_t nr = n_g - r0;
-  nr = nr > SPL_PART ? SPL_PART : nr;
-  const int64_t plane = n_g * nqp;
-  const float* base = spart + q * n_g + r0;
-  const int64_t ib = index_base + r0;
-  const bool direct = n_parts == 1;  // the part's list is the answer
-  const bool with_prev = direct && merge;
-  // the scores of rows j0 + 256 u (u < 4), slices summed in order per row
-  auto scores4 = [&](int64_t j0) -> f32x4 {
-    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int sp = 0; sp < n_split; sp += SPL_SLD) {
-      f32x4 x[SPL_SLD];
-#pragma unroll
-      for (int a = 0; a < SPL_SLD; ++a)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int64_t j = j0 + 256 * u;
-          x[a][u] = j < nr && sp + a < n_split ? base[(sp + a) * plane + j] : 0.f;
-        }
-#pragma unroll
-      for (int a = 0; a < SPL_SLD; ++a) v += x[a];
-    }
-    return v;
-  };
-  // NaN and -inf are never selected
-  auto cand_of = [&](float v, int64_t j) -> Cand {
-    return j < nr && v > -__builtin_inff() ? Cand{v, ib + j} : cand_none();
-  };
-  const int n_seg = (int)((nr + SPL_SEG - 1) / SPL_SEG);  // <= SPL_PART / SPL_SEG
-  for (int64_t jb = 0; jb < nr; jb += 1024) {
-    const f32x4 v = scores4(jb + t);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t j = jb + 256 * u + t;
-      if (j < nr) sc[j] = v[u];
-      Cand c = cand_of(v[u], j);
-#pragma unroll
-      for (int off = 8; off >= 1; off >>= 1) {
-        Cand o;
-        o.s = __shfl_xor(c.s, off, kWave);
-        o.i = __shfl_xor(c.i, off, kWave);
-        if (better(o, c)) c = o;
-      }
-      const int seg = (int)((jb + 256 * u) / SPL_SEG) + t / SPL_SEG;
-      if ((t & (SPL_SEG - 1)) == 0 && seg < n_seg) buf[seg] = c;
-    }
-  }
-  int n1 = 1;
-  while (n1 < n_seg) n1 <<= 1;
-  for (int e = n_seg + t; e < n1; e += 256) buf[e] = cand_none();
-  bitonic_cand(buf, n1);
-  const Cand tau = k <= n_seg ? buf[k - 1] : cand_none();
-  __syncthreads();
-  if (t == 0) cnt = 0;
-  __syncthreads();
-  for (int64_t j = t; j < nr; j += 256) {
-    const Cand c = cand_of(sc[j], j);
-    if (c.i >= 0 && !better(tau, c)) {
-      const int pos = atomicAdd(&cnt, 1);
-      if (pos < SPL_CAP) buf[pos] = c;
-    }
-  }
-  __syncthreads();
-  int n = cnt;
-  float* os = direct ? top_s + q * k : part_s + (q * n_parts + p) * (int64_t)k;
-  int64_t* oi = direct ? top_i + q * k : part_i + (q * n_parts + p) * (int64_t)k;
-  if (n <= SPL_CAP) {
-    if (with_prev) {
-      for (int e = t; e < k; e += 256) {
-        const Cand c{top_s[q * k + e], top_i[q * k + e]};
-        buf[n + e] = c.i >= 0 ? c : cand_none();
-      }
-      n += k;
-    }
-    int n2 = 1;
-    while (n2 < n || n2 < k) n2 <<= 1;
-    for (int e = n + t; e < n2; e += 256) buf[e] = cand_none();
-    bitonic_cand(buf, n2);
-    for (int j = t; j < k; j += 256) {
-      const Cand c = buf[j];
-      os[j] = c.i >= 0 ? c.s : -__builtin_inff();
-      oi[j] = c.i >= 0 ? c.i : -1;
-    }
-    return;
-  }
-  // fallback: round r takes the best candidate strictly after round r - 1's
-  Cand last = cand_none();
-  for (int r = 0; r < k; ++r) {
-    Cand tb = cand_none();
-    for (int64_t j = t; j < nr; j += 256) {
-      const Cand c = cand_of(sc[j], j);
-      if (c.i >= 0 && (r == 0 || better(last, c)) && better(c, tb)) tb = c;
-    }
-    if (with_prev)
-      for (int e = t; e < k; e += 256) {
-        const Cand c{top_s[q * k + e], top_i[q * k + e]};
-        if (c.i >= 0 && (r == 0 || better(last, c)) && better(c, tb)) tb = c;
-      }
-    const Cand wb = wave_best(tb);
-    if ((t & 63) == 0) wbest[t >> 6] = wb;
-    __syncthreads();
-    Cand best = wbest[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w)
-      if (better(wbest[w], best)) best = wbest[w];
-    if (t == 0) buf[r] = best;
-    last = best;
-    __syncthreads();
-  }
-  for (int j = t; j < k; j += 256) {
+// Sorts the n <= SEL_CAP candidates of buf and writes the k best as a list.
+__device__ inline void write_best(Cand* buf, int n, int k, float* os, int64_t* oi) {
+  int n2 = 1;
+  while (n2 < n || n2 < k) n2 <<= 1;
+  for (int e = n + (int)threadIdx.x; e < n2; e += SEL_NT) buf[e] = cand_none();
+  bitonic_cand(buf, n2);
+  for (int j = threadIdx.x; j < k; j += SEL_NT) {
     const Cand c = buf[j];
     os[j] = c.i >= 0 ? c.s : -__builtin_inff();
     oi[j] = c.i >= 0 ? c.i : -1;
   }
 }
 
-// One workgroup per query.  Every source list is sorted, so with d =
-// ceil(k / sources) the first d entries of all sources hold at least k
-// entries, and the k-th best of them, tau, is a lower bound on the k-th
-// best overall.  The entries at or above tau (a prefix of each source) are
-// gathered into LDS and sorted; the first k are the merged list (random
-// sources: ~k to 2k entries).  For small k, and past MERGE_CAP such entries
-// (massive ties), the merge is k rounds of block arg-max over the source
-// heads instead (at k = 100 over 512 sources: ~37 us against ~150 us; at
-// k = 10 the rounds take ~13 us against ~15-25 us).
-__global__ __launch_bounds__(256) void score_merge_kernel(const float* __restrict__ part_s,
-                                                          const int64_t* __restrict__ part_i,
-                                                          int n_parts, int k, int merge,
-                                                          float* top_s, int64_t* top_i) {
-  __shared__ Cand wb[4];
-  __shared__ float os[256];
-  __shared__ int64_t oi[256];
-  __shared__ Cand buf[MERGE_CAP];
+// Best of the block's candidates (wb: SEL_NT / 64 entries in LDS).
+__device__ inline Cand block_best(Cand c, Cand* wb) {
+  c = wave_best(c);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) wb[threadIdx.x >> 6] = c;
+  __syncthreads();
+  Cand best = wb[0];
+#pragma unroll
+  for (int w = 1; w < SEL_NT / 64; ++w)
+    if (better(wb[w], best)) best = wb[w];
+  return best;
+}
+
+// Split-K plan with more than 256 rows (a store of fewer than 32768 rows):
+// one workgroup per query sums every row's slices (slice order) into registers,
+// rows u 1024 + t in thread t.  The k-th largest of the threads' best rows is
+// reached by k distinct rows, so the k best of all are at or above it; those
+// (random stores: k to 2 k rows), and the previous list when merging, are
+// gathered into LDS and sorted.  Should more than SEL_CAP qualify (massive ties)
+// the list is built by k rounds of block arg-max instead.  What bounds it is
+// latency: 1024 threads with VPT loads in flight each; 256 threads over parts of
+// 8192 rows with sorted segment maxima, and a merge of the parts, took 96 us for
+// 10 queries x 11335 rows, k = 100, and 30 us for 64 x 4096, k = 10.
+template <int VPT>
+__global__ __launch_bounds__(SEL_NT) void score_split_select_kernel(
+    const float* __restrict__ spart, int64_t nqp, int64_t n_g, int n_split, int k, int merge,
+    int64_t index_base, float* top_s, int64_t* top_i) {
+  __shared__ Cand buf[SEL_CAP];
+  __shared__ Cand wb[SEL_NT / 64];
+  __shared__ int kcnt[48];
+  __shared__ int cnt;
+  constexpr int SL = VPT == 32 ? 1 : VPT == 16 ? 2 : 8;  // slices loaded at once
+  const int64_t q = blockIdx.x;
+  const int t = threadIdx.x;
+  const int64_t plane = n_g * nqp;
+  const float* base = spart + q * n_g;
+  float v[VPT];
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) v[u] = 0.f;
+  for (int sp = 0; sp < n_split; sp += SL) {
+    float x[SL][VPT];
+#pragma unroll
+    for (int a = 0; a < SL; ++a)
+#pragma unroll
+      for (int u = 0; u < VPT; ++u) {
+        const int64_t j = (int64_t)u * SEL_NT + t;
+        x[a][u] = j < n_g && sp + a < n_split ? base[(sp + a) * plane + j] : 0.f;
+      }
+#pragma unroll
+    for (int a = 0; a < SL; ++a)
+#pragma unroll
+      for (int u = 0; u < VPT; ++u) v[u] += x[a][u];
+  }
+  // NaN and -inf are never selected (key 0)
+  auto key_of = [&](int u) -> uint32_t {
+    const uint32_t key = fkey(v[u]);
+    return (int64_t)u * SEL_NT + t < n_g && selectable(key) ? key : 0u;
+  };
+  uint32_t best_key[1] = {0u};
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const uint32_t key = key_of(u);
+    best_key[0] = key > best_key[0] ? key : best_key[0];
+  }
+  uint32_t tau = block_kth<SEL_NT>(best_key, k, 16, kcnt);
+  tau = tau ? tau : 1u;
+  if (t == 0) cnt = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < VPT; ++u)
+    if (key_of(u) >= tau) {
+      const int pos = atomicAdd(&cnt, 1);
+      if (pos < SEL_CAP) buf[pos] = Cand{v[u], index_base + (int64_t)u * SEL_NT + t};
+    }
+  __syncthreads();
+  const int n = cnt;
+  float* os = top_s + q * k;
+  int64_t* oi = top_i + q * k;
+  if (n + (merge ? k : 0) <= SEL_CAP) {
+    if (merge)
+      for (int e = t; e < k; e += SEL_NT) {
+        const Cand c{os[e], oi[e]};
+        buf[n + e] = c.i >= 0 ? c : cand_none();
+      }
+    write_best(buf, n + (merge ? k : 0), k, os, oi);
+    return;
+  }
+  // fallback: round r takes the best candidate strictly after round r - 1's
+  Cand last = cand_none();
+  for (int r = 0; r < k; ++r) {
+    Cand tb = cand_none();
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+      const Cand c = key_of(u) ? Cand{v[u], index_base + (int64_t)u * SEL_NT + t} : cand_none();
+      if (c.i >= 0 && (r == 0 || better(last, c)) && better(c, tb)) tb = c;
+    }
+    if (merge && t < k) {
+      const Cand c{os[t], oi[t]};
+      if (c.i >= 0 && (r == 0 || better(last, c)) && better(c, tb)) tb = c;
+    }
+    last = block_best(tb, wb);
+    if (t == 0) buf[r] = last;
+  }
+  __syncthreads();
+  for (int j = t; j < k; j += SEL_NT) {
+    const Cand c = buf[j];
+    os[j] = c.i >= 0 ? c.s : -__builtin_inff();
+    oi[j] = c.i >= 0 ? c.i : -1;
+  }
+}
+
+// One workgroup per query merges n_parts + merge <= 1024 sorted lists.  The
+// first d entries of every list (as many as 4096 entries allow, so at least k in
+// all) are loaded side by side; the k-th best of them is a lower bound on the
+// k-th best overall, and the entries at or above it (a prefix of each list; past
+// d entries the list's last thread goes on alone) are gathered into LDS and
+// sorted.  Past SEL_CAP such entries (massive ties) the merge is k rounds of
+// block arg-max over the list heads instead.  Latency-bound: one thread per list
+// walking its prefix, between two sorts of 256 threads, took 30-41 us at k = 100
+// over 512 lists as over two.
+constexpr int MERGE_E = 4;  // entries per thread of the first load
+__global__ __launch_bounds__(SEL_NT) void score_merge_kernel(const float* __restrict__ part_s,
+                                                             const int64_t* __restrict__ part_i,
+                                                             int n_parts, int k, int merge,
+                                                             float* top_s, int64_t* top_i) {
+  __shared__ Cand buf[SEL_CAP];
+  __shared__ Cand wb[SEL_NT / 64];
+  __shared__ int kcnt[48];
   __shared__ int cnt;
   const int64_t q = blockIdx.x;
   const int t = threadIdx.x;
   const int n_src = n_parts + (merge ? 1 : 0);
-  const float* src_s[MERGE_SPT];
-  const int64_t* src_i[MERGE_SPT];
-  int head[MERGE_SPT];
-  Cand cur[MERGE_SPT];
+  auto list_s = [&](int src) { return src < n_parts ? part_s + (q * n_parts + src) * (int64_t)k : top_s + q * (int64_t)k; };
+  auto list_i = [&](int src) { return src < n_parts ? part_i + (q * n_parts + src) * (int64_t)k : top_i + q * (int64_t)k; };
+  auto entry = [&](int src, int j) { return Cand{list_s(src)[j], list_i(src)[j]}; };
+  const int room = n_src > 0 ? MERGE_E * SEL_NT / n_src : k;
+  const int d = room < k ? room : k;
+  Cand e4[MERGE_E];
+  uint32_t key[MERGE_E];
 #pragma unroll
-  for (int m = 0; m < MERGE_SPT; ++m) {
-    const int src = t + 256 * m;
-    src_s[m] = nullptr;
-    src_i[m] = nullptr;
-    if (src < n_parts) {
-      src_s[m] = part_s + (q * n_parts + src) * (int64_t)k;
-      src_i[m] = part_i + (q * n_parts + src) * (int64_t)k;
-    } else if (src < n_src) {
-      src_s[m] = top_s + q * (int64_t)k;
-      src_i[m] = top_i + q * (int64_t)k;
-    }
-    head[m] = 0;
-    cur[m] = src_s[m] ? Cand{src_s[m][0], src_i[m][0]} : Cand{-__builtin_inff(), -1};
+  for (int m = 0; m < MERGE_E; ++m) {
+    const int e = t + SEL_NT * m, src = e / d;
+    e4[m] = src < n_src ? entry(src, e - src * d) : cand_none();
+    // (a caller's previous list may hold -inf, or anything, under a valid index)
+    key[m] = e4[m].i < 0 ? 0u : e4[m].s == e4[m].s ? fkey(e4[m].s) : 1u;
   }
-  const Cand none{-__builtin_inff(), -1};
-  if (k > MERGE_ROUNDS_K) {
-    // tau: the k-th best of the first d entries of every source
-    const int d = n_src > 0 ? (k + n_src - 1) / n_src : 1;
-    int n1 = 1;
-    while (n1 < n_src * d) n1 <<= 1;
-    for (int e = t; e < n1; e += 256) {
-      const int src = e / d, j = e - src * d;
-      Cand c = none;
-      if (src < n_src) {
-        const float* ps = src < n_parts ? part_s + (q * n_parts + src) * (int64_t)k : top_s + q * (int64_t)k;
-        const int64_t* pi = src < n_parts ? part_i + (q * n_parts + src) * (int64_t)k : top_i + q * (int64_t)k;
-        c = Cand{ps[j], pi[j]};
-      }
-      buf[e] = c;
-    }
-    bitonic_cand(buf, n1);
-    const Cand tau = buf[k - 1];
-    if (t == 0) cnt = 0;
-    __syncthreads();
-    // gather the entries at or above tau (every valid one when tau is empty),
-    // four entries of a source per load round
+  uint32_t tau = block_kth<SEL_NT>(key, k, 16, kcnt);
+  tau = tau ? tau : 1u;
+  if (t == 0) cnt = 0;
+  __syncthreads();
+  auto take = [&](const Cand& c) {
+    const int pos = atomicAdd(&cnt, 1);
+    if (pos < SEL_CAP) buf[pos] = c;
+  };
 #pragma unroll
-    for (int m = 0; m < MERGE_SPT; ++m) {
-      if (!src_s[m]) continue;
-      bool go = true;
-      for (int j0 = 0; go && j0 < k; j0 += 4) {
-        Cand e4[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) e4[u] = j0 + u < k ? Cand{src_s[m][j0 + u], src_i[m][j0 + u]} : none;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (!go) break;
-          if (e4[u].i < 0 || better(tau, e4[u])) {
-            go = false;
-          } else {
-            const int pos = atomicAdd(&cnt, 1);
-            if (pos < MERGE_CAP) buf[pos] = e4[u];
-          }
+  for (int m = 0; m < MERGE_E; ++m)
+    if (key[m] >= tau) {
+      take(e4[m]);
+      const int e = t + SEL_NT * m, src = e / d;
+      if (e - src * d == d - 1)
+        for (int j = d; j < k; ++j) {
+          const Cand c = entry(src, j);
+          if (c.i < 0 || fkey(c.s) < tau) break;
+          take(c);
         }
-      }
     }
-    __syncthreads();
-    const int n = cnt;
-    if (n <= MERGE_CAP) {
-      int n2 = 1;
-      while (n2 < n || n2 < k) n2 <<= 1;
-      for (int e = n + t; e < n2; e += 256) buf[e] = none;
-      bitonic_cand(buf, n2);
-      for (int j = t; j < k; j += 256) {
-        const Cand c = buf[j];
-        top_s[q * (int64_t)k + j] = c.i >= 0 ? c.s : -__builtin_inff();
-        top_i[q * (int64_t)k + j] = c.i >= 0 ? c.i : -1;
-      }
-      return;
-    }
+  __syncthreads();
+  const int n = cnt;
+  float* os = top_s + q * (int64_t)k;
+  int64_t* oi = top_i + q * (int64_t)k;
+  if (n <= SEL_CAP) {
+    write_best(buf, n, k, os, oi);
+    return;
   }
+  int head = 0;
+  Cand cur = t < n_src ? entry(t, 0) : cand_none();
   for (int j = 0; j < k; ++j) {
-    // this thread's best head
-    Cand tb = cur[0];
-    int tm = 0;
-#pragma unroll
-    for (int m = 1; m < MERGE_SPT; ++m)
-      if (better(cur[m], tb)) {
-        tb = cur[m];
-        tm = m;
-      }
-    Cand b = wave_best(tb);
-    if ((t & 63) == 0) wb[t >> 6] = b;
-    __syncthreads();
-    Cand best = wb[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w)
-      if (better(wb[w], best)) best = wb[w];
-    if (t == 0) {
-      os[j] = best.i >= 0 ? best.s : -__builtin_inff();
-      oi[j] = best.i;
+    const Cand best = block_best(cur, wb);
+    if (t == 0) buf[j] = best;
+    // the list whose head won advances (indices are unique across lists)
+    if (best.i >= 0 && cur.i == best.i && cur.s == best.s) {
+      ++head;
+      cur = head < k ? entry(t, head) : cand_none();
     }
-    // the source whose head won advances (indices are unique across sources)
-    if (best.i >= 0 && tb.i == best.i && tb.s == best.s) {
-#pragma unroll
-      for (int m = 0; m < MERGE_SPT; ++m)
-        if (m == tm) {
-          ++head[m];
-          cur[m] = head[m] < k ? Cand{src_s[m][head[m]], src_i[m][head[m]]} : Cand{-__builtin_inff(), -1};
-        }
-    }
-    __syncthreads();
   }
-  for (int j = t; j < k; j += 256) {
-    top_s[q * (int64_t)k + j] = os[j];
-    top_i[q * (int64_t)k + j] = oi[j];
+  __syncthreads();
+  for (int j = t; j < k; j += SEL_NT) {
+    const Cand c = buf[j];
+    os[j] = c.i >= 0 ? c.s : -__builtin_inff();
+    oi[j] = c.i >= 0 ? c.i : -1;
   }
 }
 
@@ -1394,9 +1363,8 @@ ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes)
     // the output (no partition lists): n_g < 256 x 128 rows here
     P.split = (int)split;
     P.n_tiles = (int)n_tiles;
-    P.rows_per_part = SPL_PART;
-    P.n_parts = (int)((n_g + SPL_PART - 1) / SPL_PART);
-    if (P.n_parts == 1) P.n_parts = 0;  // one part: its list is the answer (no partition lists)
+    P.rows_per_part = n_g;
+    P.n_parts = 0;  // no partition lists
     P.spart_bytes = (size_t)split * (size_t)n_g * (size_t)P.n_qb * SQB * 4;
   } else {
     P.split = 1;
@@ -1433,12 +1401,17 @@ ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes)
 // fewer than k are finite).  One workgroup per query; nb <= 1024.
 __global__ __launch_bounds__(256) void score_bound_kernel(const float* __restrict__ seg_s, int nb, int k,
                                                           float* __restrict__ bound) {
-  __shared__ float v[1024];
+  __shared__ int kcnt[48];
   const int64_t q = blockIdx.x;
-  for (int i = threadIdx.x; i < 1024; i += 256) v[i] = i < nb ? seg_s[q * nb + i] : -__builtin_inff();
-  __syncthreads();
-  bitonic_desc(v, 1024);
-  if (threadIdx.x == 0) bound[q] = v[k - 1];
+  uint32_t key[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int i = (int)threadIdx.x + 256 * u;
+    const uint32_t x = i < nb ? fkey(seg_s[q * nb + i]) : 0u;
+    key[u] = selectable(x) ? x : 0u;
+  }
+  const uint32_t kth = block_kth<256>(key, k, 0, kcnt);
+  if (threadIdx.x == 0) bound[q] = kth ? fkey_inv(kth) : -__builtin_inff();
 }
 
 hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int64_t n_q,
@@ -1543,14 +1516,20 @@ hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int
     if (e != hipSuccess) return e;
   } else if (n_g > 0) {
     dim3 grid((unsigned)((int64_t)plan.n_qb * plan.n_tiles * plan.split)), block(256);
-    if (f16)
-      hipLaunchKernelGGL(score_splitk_kernel<true>, grid, block, 0, s, (const char*)Q, n_q, ldq,
-                         (const char*)G, n_g, ldg, plan.n_grp, plan.n_qb, plan.n_tiles, plan.split,
-                         spart);
-    else
-      hipLaunchKernelGGL(score_splitk_kernel<false>, grid, block, 0, s, (const char*)Q, n_q, ldq,
-                         (const char*)G, n_g, ldg, plan.n_grp, plan.n_qb, plan.n_tiles, plan.split,
-                         spart);
+#define ATTR_SK(F, QT)                                                                               \
+  hipLaunchKernelGGL((score_splitk_kernel<F, QT>), grid, block, 0, s, (const char*)Q, n_q, ldq,      \
+                     (const char*)G, n_g, ldg, plan.n_grp, plan.n_qb, plan.n_tiles, plan.split, spart)
+    if (n_q <= 16) {
+      if (f16) ATTR_SK(true, 1);
+      else ATTR_SK(false, 1);
+    } else if (n_q <= 32) {
+      if (f16) ATTR_SK(true, 2);
+      else ATTR_SK(false, 2);
+    } else {
+      if (f16) ATTR_SK(true, 4);
+      else ATTR_SK(false, 4);
+    }
+#undef ATTR_SK
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (n_g <= 256) {
@@ -1559,14 +1538,19 @@ hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int
                          merge, index_base, top_s, top_i);
       return hipGetLastError();
     }
-    const int np = plan.n_parts > 0 ? plan.n_parts : 1;
-    hipLaunchKernelGGL(score_split_topk_kernel, dim3((unsigned)(n_q * np)), dim3(256), 0, s,
-                       (const float*)spart, (int64_t)plan.n_qb * SQB, n_g, plan.split, k, merge,
-                       index_base, np, part_s, part_i, top_s, top_i);
-    e = hipGetLastError();
-    if (e != hipSuccess || np == 1) return e;
+#define ATTR_SEL(V)                                                                              \
+  hipLaunchKernelGGL(score_split_select_kernel<V>, dim3((unsigned)n_q), dim3(SEL_NT), 0, s,     \
+                     (const float*)spart, (int64_t)plan.n_qb * SQB, n_g, plan.split, k, merge,  \
+                     index_base, top_s, top_i)
+    if (n_g <= SEL_NT) ATTR_SEL(1);
+    else if (n_g <= 4 * SEL_NT) ATTR_SEL(4);
+    else if (n_g <= 16 * SEL_NT) ATTR_SEL(16);
+    else if (n_g <= 32 * SEL_NT) ATTR_SEL(32);
+    else return hipErrorInvalidConfiguration;  // the plan splits fewer than 32768 rows
+#undef ATTR_SEL
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(score_merge_kernel, dim3((unsigned)n_q), dim3(256), 0, s,
+  hipLaunchKernelGGL(score_merge_kernel, dim3((unsigned)n_q), dim3(SEL_NT), 0, s,
                      (const float*)part_s, (const int64_t*)part_i, n_parts, k, merge, top_s, top_i);
   return hipGetLastError();
 }
