@@ -255,14 +255,137 @@ __global__ __launch_bounds__(256) void rowscale2_kernel(const TX* __restrict__ X
   }
 }
 
+// The same for rows of more than 8192 columns: R rows per workgroup of TPR
+// threads, CH chunks of 8 elements per thread and row, kept as loaded between
+// the norm and the write, so that every row's loads are in flight at once; the
+// scale is read once per R rows.  Bound by the memory's mixed read and write
+// rate (a device copy reaches 5.1-5.2 TB/s).  Against one row per 256 threads,
+// which reads 48 KB of scale with every 24 KB row: 200000 x 12288 DIAG in fp16
+// 1817 -> 1730 us (5.7 TB/s), 20000 x 24096 574 -> 386 us (5.0 TB/s) and, without
+// a scale, 459 -> 338 us.  Four rows, 256 threads, or a loop over rows with the
+// scale in registers were no faster (1776, 1743, 1742 us).
+// Raw: the 8 elements of a chunk as loaded.
+template <typename T>
+struct RawChunk;
+template <>
+struct RawChunk<float> {
+  f32x4 a, b;
+  __device__ inline void load(const float* p) {
+    a = __builtin_nontemporal_load((const f32x4*)p);
+    b = __builtin_nontemporal_load((const f32x4*)(p + 4));
+  }
+  __device__ inline void get(float (&v)[8]) const {
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  }
+};
+template <>
+struct RawChunk<_Float16> {
+  f16x8 a;
+  __device__ inline void load(const _Float16* p) { a = __builtin_nontemporal_load((const f16x8*)p); }
+  __device__ inline void get(float (&v)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
+  }
+};
+
+template <typename TX, typename TY, int TPR, int CH, int R, bool DIAG>
+__global__ __launch_bounds__(TPR) void rowscale_rows_kernel(
+    const TX* X, int64_t ldx, int64_t n_rows, int64_t D, const float* __restrict__ m, int unit,
+    TY* Y, int64_t ldy) {
+  constexpr int NW = TPR / 64;
+  __shared__ float sh[R][NW];
+  const int t = (int)threadIdx.x;
+  const int n8 = (int)(D / 8);
+  const int64_t r0 = (int64_t)blockIdx.x * R;
+  RawChunk<TX> x[R][CH];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+      if (r0 + i < n_rows && t + j * TPR < n8) x[i][j].load(X + (r0 + i) * ldx + (int64_t)(t + j * TPR) * 8);
+  float mm[DIAG ? CH : 1][8];
+  if (DIAG) {
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+      if (t + j * TPR < n8) load8<float>(m + (int64_t)(t + j * TPR) * 8, mm[DIAG ? j : 0]);
+  }
+  auto value = [&](int i, int j, float (&v)[8]) {
+    x[i][j].get(v);
+    if (DIAG) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= mm[DIAG ? j : 0][e];
+    }
+  };
+  float ss[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) ss[i] = 0.f;
+  if (unit) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+#pragma unroll
+      for (int j = 0; j < CH; ++j)
+        if (r0 + i < n_rows && t + j * TPR < n8) {
+          float v[8];
+          value(i, j, v);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ss[i] += v[e] * v[e];
+        }
+      ss[i] = wave_sum(ss[i]);
+      if ((t & 63) == 0) sh[i][t >> 6] = ss[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      ss[i] = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) ss[i] += sh[i][w];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (r0 + i >= n_rows) break;  // uniform
+    const float sc = row_scale(ss[i], unit);
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+      if (t + j * TPR < n8) {
+        float v[8];
+        value(i, j, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= sc;
+        store8<TY>(Y + (r0 + i) * ldy + (int64_t)(t + j * TPR) * 8, v);
+      }
+  }
+}
+
 template <typename TX, typename TY>
 hipError_t launch_rowscale_t(const void* X, int64_t ldx, int64_t n_rows, int64_t D,
                              const float* m, int unit, const float* row_ss, const int8_t* seg_e,
                              int64_t n_ss, void* Y, int64_t ldy, hipStream_t s) {
-  dim3 grid((unsigned)n_rows), block(256);
   const int64_t n8 = D / 8;
   const TX* x = (const TX*)X;
   TY* y = (TY*)Y;
+#define ATTR_RR(T, C, R, DG)                                                                       \
+  {                                                                                                \
+    hipLaunchKernelGGL((rowscale_rows_kernel<TX, TY, T, C, R, DG>), dim3((unsigned)((n_rows + R - 1) / R)), \
+                       dim3(T), 0, s, x, ldx, n_rows, D, m, unit, y, ldy);                         \
+    return hipGetLastError();                                                                      \
+  }
+  if (!row_ss && n8 <= 4096) {
+    if (m && n8 > 1024) {  // (up to 1024: the two-row kernel below)
+      if (n8 <= 1536) ATTR_RR(512, 3, 2, true)
+      if (n8 <= 2048) ATTR_RR(512, 4, 2, true)
+      if (n8 <= 3072) ATTR_RR(1024, 3, 2, true)
+      ATTR_RR(1024, 4, 2, true)
+    }
+    // without a scale one row per 256 threads is as fast up to 16384 columns
+    if (!m && n8 > 2048) {
+      if (n8 <= 3072) ATTR_RR(1024, 3, 1, false)
+      ATTR_RR(1024, 4, 1, false)
+    }
+  }
+#undef ATTR_RR
+  dim3 grid((unsigned)n_rows), block(256);
 #define ATTR_RS(CH) \
   hipLaunchKernelGGL((rowscale_kernel<TX, TY, CH>), grid, block, 0, s, x, ldx, D, m, unit, row_ss, \
                      seg_e, n_ss, y, ldy)
@@ -290,72 +413,86 @@ hipError_t launch_rowscale_t(const void* X, int64_t ldx, int64_t n_rows, int64_t
 // ---------------------------------------------------------------------------
 // colsumsq
 // ---------------------------------------------------------------------------
-constexpr int kColBlock = 256 * 8;  // columns per workgroup
+constexpr int kColThreads = 256;
+// columns per workgroup: one 16-byte load per thread and row (fp32 rows in two
+// 16-byte halves per thread touched every cache line twice: 247043 x 4544 in
+// fp32 895 -> 745 us, 4.9 -> 6.0 TB/s)
+constexpr int col_block(int elem_bytes) { return kColThreads * (16 / elem_bytes); }
+constexpr int kColRows = 8;  // rows in flight per thread (16: no faster)
 
-template <typename TX>
+// VE: elements per 16-byte load
+template <typename TX, int VE>
 __global__ __launch_bounds__(256) void colsumsq_kernel(const TX* __restrict__ X, int64_t ldx,
                                                        int64_t n_rows, int64_t D,
                                                        int64_t rows_per_panel,
                                                        double* __restrict__ part) {
-  const int64_t c0 = (int64_t)blockIdx.x * kColBlock + (int64_t)threadIdx.x * 8;
+  typedef TX vec __attribute__((ext_vector_type(VE)));
+  const int64_t c0 = ((int64_t)blockIdx.x * kColThreads + threadIdx.x) * VE;
   const int64_t panel = blockIdx.y;
   if (c0 >= D) return;
   const int64_t r0 = panel * rows_per_panel;
   int64_t r1 = r0 + rows_per_panel;
   r1 = r1 > n_rows ? n_rows : r1;
-  double acc[8];
+  double acc[VE];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+  for (int e = 0; e < VE; ++e) acc[e] = 0.0;
+  auto load = [&](int64_t r) {
+    return __builtin_bit_cast(vec, __builtin_nontemporal_load((const i32x4*)(X + r * ldx + c0)));
+  };
   int64_t r = r0;
-  for (; r + 8 <= r1; r += 8) {
-    float v[8][8];
+  for (; r + kColRows <= r1; r += kColRows) {
+    vec v[kColRows];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) load8_nt<TX>(X + (r + u) * ldx + c0, v[u]);
-    float f[8];
+    for (int u = 0; u < kColRows; ++u) v[u] = load(r + u);
+    // fp32 sums over 8 rows
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      f[e] = 0.f;
+    for (int e = 0; e < VE; ++e) {
+      float f = 0.f;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) f[e] += v[u][e] * v[u][e];
-      acc[e] += (double)f[e];
+      for (int u = 0; u < kColRows; ++u) f += (float)v[u][e] * (float)v[u][e];
+      acc[e] += (double)f;
     }
   }
   for (; r < r1; ++r) {
-    float v[8];
-    load8<TX>(X + r * ldx + c0, v);
+    const vec v = load(r);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += (double)(v[e] * v[e]);
+    for (int e = 0; e < VE; ++e) acc[e] += (double)((float)v[e] * (float)v[e]);
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) part[panel * D + c0 + e] = acc[e];
+  for (int e = 0; e < VE; ++e) part[panel * D + c0 + e] = acc[e];
 }
 
-// h_j += sum over panels of part[p][j]: a workgroup takes 64 columns, wave w
-// sums panels p = w (mod 4) in increasing order (each panel read as 512
-// contiguous bytes per wave), and the four sums are added in wave order:
-// a fixed order, so the result is deterministic.
-__global__ __launch_bounds__(256) void colsumsq_final_kernel(const double* __restrict__ part,
-                                                             int64_t n_panels, int64_t D,
-                                                             float* __restrict__ H) {
-  __shared__ double red[4][64];
-  const int w = threadIdx.x >> 6, c = threadIdx.x & 63;
+// h_j += sum over panels of part[p][j]: a workgroup takes 64 columns, wave w of
+// nw sums panels p = w (mod nw) in increasing order (each panel read as 512
+// contiguous bytes per wave), and the sums are added in wave order: a fixed
+// order, so the result is deterministic.  Sixteen waves from 512 panels on (few
+// columns, so few workgroups: with four, the 2048 panels of 1672 columns were a
+// chain of 128 load rounds on 27 workgroups, 45 us).
+constexpr int kFinWaves = 16;
+__global__ __launch_bounds__(64 * kFinWaves) void colsumsq_final_kernel(const double* __restrict__ part,
+                                                                        int64_t n_panels, int64_t D,
+                                                                        float* __restrict__ H) {
+  __shared__ double red[kFinWaves][64];
+  const int w = threadIdx.x >> 6, c = threadIdx.x & 63, nw = blockDim.x >> 6;
   const int64_t j = (int64_t)blockIdx.x * 64 + c;
   double s = 0.0;
   if (j < D) {
     int64_t p = w;
-    for (; p + 12 < n_panels; p += 16) {
-      const double v0 = part[p * D + j], v1 = part[(p + 4) * D + j];
-      const double v2 = part[(p + 8) * D + j], v3 = part[(p + 12) * D + j];
-      s += v0;
-      s += v1;
-      s += v2;
-      s += v3;
+    for (; p + 3 * nw < n_panels; p += 4 * nw) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = part[(p + u * nw) * D + j];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += v[u];
     }
-    for (; p < n_panels; p += 4) s += part[p * D + j];
+    for (; p < n_panels; p += nw) s += part[p * D + j];
   }
   red[w][c] = s;
   __syncthreads();
-  if (w == 0 && j < D) H[j] = (float)((double)H[j] + (((red[0][c] + red[1][c]) + red[2][c]) + red[3][c]));
+  if (w == 0 && j < D) {
+    for (int u = 1; u < nw; ++u) s += red[u][c];
+    H[j] = (float)((double)H[j] + s);
+  }
 }
 
 }  // namespace
@@ -377,7 +514,7 @@ hipError_t launch_rowscale(int x_dtype, int y_dtype, const void* X, int64_t ldx,
 }
 
 int colsumsq_panels(int64_t n_rows, int64_t D) {
-  const int64_t ncb = (D + kColBlock - 1) / kColBlock;
+  const int64_t ncb = (D + col_block(2) - 1) / col_block(2);
   int64_t panels = (2048 + ncb - 1) / ncb;
   const int64_t max_by_rows = (n_rows + 63) / 64;  // at least 64 rows per panel
   if (panels > max_by_rows) panels = max_by_rows;
@@ -390,17 +527,18 @@ hipError_t launch_colsumsq(int x_dtype, const void* X, int64_t ldx, int64_t n_ro
                            float* H, double* part, hipStream_t s) {
   const int panels = colsumsq_panels(n_rows, D);
   const int64_t rpp = (n_rows + panels - 1) / panels;
-  dim3 grid((unsigned)((D + kColBlock - 1) / kColBlock), (unsigned)panels), block(256);
+  const int cb = col_block(x_dtype == 0 ? 4 : 2);
+  dim3 grid((unsigned)((D + cb - 1) / cb), (unsigned)panels), block(kColThreads);
   if (x_dtype == 0)
-    hipLaunchKernelGGL(colsumsq_kernel<float>, grid, block, 0, s, (const float*)X, ldx, n_rows, D, rpp, part);
+    hipLaunchKernelGGL((colsumsq_kernel<float, 4>), grid, block, 0, s, (const float*)X, ldx, n_rows, D, rpp, part);
   else if (x_dtype == 1)
-    hipLaunchKernelGGL(colsumsq_kernel<__bf16>, grid, block, 0, s, (const __bf16*)X, ldx, n_rows, D, rpp, part);
+    hipLaunchKernelGGL((colsumsq_kernel<__bf16, 8>), grid, block, 0, s, (const __bf16*)X, ldx, n_rows, D, rpp, part);
   else
-    hipLaunchKernelGGL(colsumsq_kernel<_Float16>, grid, block, 0, s, (const _Float16*)X, ldx, n_rows, D, rpp, part);
+    hipLaunchKernelGGL((colsumsq_kernel<_Float16, 8>), grid, block, 0, s, (const _Float16*)X, ldx, n_rows, D, rpp, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   dim3 g2((unsigned)((D + 63) / 64));
-  hipLaunchKernelGGL(colsumsq_final_kernel, g2, block, 0, s, (const double*)part, (int64_t)panels, D, H);
+  hipLaunchKernelGGL(colsumsq_final_kernel, g2, dim3(panels >= 512 ? 64 * kFinWaves : 256), 0, s, (const double*)part, (int64_t)panels, D, H);
   return hipGetLastError();
 }
 
