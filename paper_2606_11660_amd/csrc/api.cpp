@@ -287,16 +287,16 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
         e.g = m.g;
         e.R = m.R;
         e.S = m.S;
-        e.lda = m.lda;
-        e.ldg = m.ldg;
+        e.lda = (int32_t)m.lda;
+        e.ldg = (int32_t)m.ldg;
         e.out_col = m.out_col;
-        e.pk_off = (int64_t)L.pk_off[s0 + j];
+        e.pk_off = (uint32_t)(L.pk_off[s0 + j] / 256);  // module fragments are 256-byte aligned
         e.d_in = (int32_t)m.d_in;
         e.d_out = (int32_t)m.d_out;
         e.v_out = m.v_out;
         e.v_in = m.v_in;
-        e.grp = L.slot_grp[s0 + j];
-        e.lead_ms = L.lead_ms[s0 + j];
+        e.grp = (int16_t)L.slot_grp[s0 + j];
+        e.lead_ms = (int16_t)L.lead_ms[s0 + j];
       }
       hipError_t e = attr::launch_project_pack(bf16, nk, pa, tab, gtab, pk, s);
       if (e != hipSuccess) return device_fail(e, "attr_project pack launch");

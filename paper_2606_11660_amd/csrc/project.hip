@@ -84,6 +84,7 @@ __device__ inline uint16_t bf16_rne(float x) {
 // (j = lane % 16, grp = lane / 16) holds rows KS*ks + E*grp + e (e < E) of
 // column 16*ct + j, where E = 16 / elem_bytes and KS = 4 E.
 // ---------------------------------------------------------------------------
+constexpr int kPackSplit = 8;
 template <bool BF16, int NK>
 __global__ __launch_bounds__(256) void project_pack_kernel(PackArgs args, ProjTab* tab,
                                                            ProjGroup* gtab, char* pk_base) {
@@ -94,10 +95,11 @@ __global__ __launch_bounds__(256) void project_pack_kernel(PackArgs args, ProjTa
   const int j = blockIdx.x;
   if (j >= args.n) return;
   const PackEntry pe = args.e[j];
-  char* pk = pk_base + pe.pk_off;
-  // blockIdx.y splits a module's fragments over gridDim.y workgroups
-  const int f0 = (int)(blockIdx.y * blockDim.x + threadIdx.x);
-  const int fstep = (int)(gridDim.y * blockDim.x);
+  char* pk = pk_base + (size_t)pe.pk_off * 256;
+  // blockIdx.y splits a module's fragments over kPackSplit workgroups (launch
+  // sizes as constants: the arguments leave no room for hidden ones)
+  const int f0 = (int)(blockIdx.y * 256 + threadIdx.x);
+  constexpr int fstep = kPackSplit * 256;
   if (blockIdx.y == 0 && threadIdx.x == 0) {
     ProjTab t;
     t.a = pe.a;
@@ -121,7 +123,7 @@ __global__ __launch_bounds__(256) void project_pack_kernel(PackArgs args, ProjTa
   if (norm) {
     __shared__ double red[256];
     double acc = 0.0;
-    for (int i = threadIdx.x; i < pe.d_out; i += blockDim.x) {
+    for (int i = threadIdx.x; i < pe.d_out; i += 256) {
       const float x = pe.v_out[i];
       acc += x > 0.f ? (double)x : 0.0;
     }
@@ -845,7 +847,7 @@ size_t project_packed_bytes(int64_t d_in, int64_t d_out, int k, int elem_bytes) 
 
 hipError_t launch_project_pack(bool bf16, int nk, const PackArgs& args, ProjTab* tab,
                                ProjGroup* gtab, char* pk_base, hipStream_t s) {
-  dim3 grid(args.n, 8), block(256);
+  dim3 grid(args.n, kPackSplit), block(256);
 #define ATTR_PACK(B, N) \
   hipLaunchKernelGGL((project_pack_kernel<B, N>), grid, block, 0, s, args, tab, gtab, pk_base)
   if (bf16) {
