@@ -520,9 +520,10 @@ struct ScoreLayout {
   size_t off_s, off_i, off_p, total;
 };
 
-static ScoreLayout score_layout(int64_t n_q, int64_t n_g, int64_t D, int32_t k, int eb) {
+static ScoreLayout score_layout(int64_t n_q, int64_t n_g, int64_t D, int32_t k, int eb,
+                                bool fewest_bytes = false) {
   ScoreLayout L{};
-  L.plan = attr::plan_score(n_q, n_g, D, k, eb);
+  L.plan = attr::plan_score(n_q, n_g, D, k, eb, fewest_bytes);
   if (n_q <= 0 || n_g <= 0) return L;
   const size_t n = L.plan.list_entries;
   L.off_s = 0;
@@ -534,9 +535,11 @@ static ScoreLayout score_layout(int64_t n_q, int64_t n_g, int64_t D, int32_t k, 
 
 size_t attr_score_topk_workspace_size(int64_t n_q, int64_t n_g, int64_t D, int32_t k) {
   if (n_q < 0 || n_g < 0 || k < 1 || k > 128 || D < 1) return 0;
-  // the fp16 plan needs at least as much workspace as the fp32 plan
-  const ScoreLayout a = score_layout(n_q, n_g, D, k, 2), b = score_layout(n_q, n_g, D, k, 4);
-  return a.total > b.total ? a.total : b.total;
+  size_t total = 0;
+  for (const int eb : {2, 4})
+    for (const bool fewest : {false, true})
+      total = std::max(total, score_layout(n_q, n_g, D, k, eb, fewest).total);
+  return total;
 }
 
 attr_status attr_score_topk(const void* Q, int64_t n_q, int64_t ldq, const void* G, int64_t n_g,
@@ -574,7 +577,8 @@ attr_status attr_score_topk(const void* Q, int64_t n_q, int64_t ldq, const void*
       return fail(ATTR_ERR_INVALID_ARG, "top_score / top_index overlap each other or the inputs");
     if (n_q == 0) return ATTR_OK;
     if (n_g == 0 && merge) return ATTR_OK;
-    const ScoreLayout L = score_layout(n_q, n_g, D, k, eb);
+    ScoreLayout L = score_layout(n_q, n_g, D, k, eb);
+    if (L.total > (ws ? ws_bytes : 0)) L = score_layout(n_q, n_g, D, k, eb, true);
     if (L.total > 0 && (!ws || ws_bytes < L.total))
       return fail(ATTR_ERR_WORKSPACE, "attr_score_topk needs %zu workspace bytes", L.total);
     if (reinterpret_cast<uintptr_t>(ws) & 255u)

@@ -135,7 +135,8 @@ hipError_t launch_colsumsq(int x_dtype, const void* X, int64_t ldx, int64_t n_ro
 struct ScorePlan {
   int n_qb;              // query blocks of 64 queries
   int n_grp;             // 128-byte K-groups per row
-  int split;             // D-slices (1: fused plan)
+  int split_plan;        // split-K plan (else: streaming or GEMM)
+  int split;             // its D-slices
   int n_tiles;           // 128-row tiles (split-K plan)
   int n_parts;           // row partitions, one sorted list each per query
   int64_t rows_per_part;
@@ -146,7 +147,8 @@ struct ScorePlan {
   int64_t D;
   int64_t bound_rows;    // streaming plan: rows of the prefix scan that bounds the k-th best (0: none)
 };
-ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes);
+// fewest_bytes: no plan that takes more workspace for speed
+ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes, bool fewest_bytes);
 hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int64_t n_q,
                              int64_t ldq, const void* G, int64_t n_g, int64_t ldg, int k,
                              int64_t index_base, int merge, float* top_s, int64_t* top_i,

@@ -1307,7 +1307,7 @@ static StreamCfg stream_cfg(int64_t n_q, int k) {
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 constexpr int64_t BOUND_ROWS = 16384;  // prefix rows whose segment maxima bound the k-th best
 
-ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes) {
+ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes, bool fewest_bytes) {
   ScorePlan P{};
   P.D = D;
   P.n_qb = (int)((n_q + SQB - 1) / SQB);
@@ -1358,10 +1358,16 @@ ScorePlan plan_score(int64_t n_q, int64_t n_g, int64_t D, int k, int elem_bytes)
     const int64_t cap = ((int64_t)256 << 20) / ((int64_t)n_g * P.n_qb * SQB * 4);
     split = split > cap ? cap : split;
   }
-  if (split >= 2) {
+  // Rows of fewer than 16 groups are not split, but take the same two kernels
+  // where the workspace holds their scores (a workspace of the streaming plan's
+  // size takes that one): streaming / these, 8 queries x 256 rows x 256 in fp32
+  // 34 / 13 us, 64 x 2000 x 512, k = 100, 346 / 28, 100 x 10000 x 64 151 / 18, 1
+  // x 32000 x 64 15.1 / 14.3.
+  if (split >= 2 || (P.n_qb * n_tiles < 256 && !fewest_bytes)) {
     // partial slices, then one selection workgroup per query straight into
     // the output (no partition lists): n_g < 256 x 128 rows here
     P.split = (int)split;
+    P.split_plan = 1;
     P.n_tiles = (int)n_tiles;
     P.rows_per_part = n_g;
     P.n_parts = 0;  // no partition lists
@@ -1445,7 +1451,7 @@ hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-  } else if (n_g > 0 && plan.split <= 1) {
+  } else if (n_g > 0 && !plan.split_plan) {
     // lower bound on each query's k-th best score: the k-th largest of the
     // maxima of the first bound_rows / 64 row segments (k distinct rows reach
     // it).  The maxima come from this kernel run with k = 1 over one-tile
