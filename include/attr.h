@@ -152,14 +152,16 @@ attr_status attr_project_tokens(const attr_module* mods, int32_t n_mods, attr_dt
 /* attr_project without a workspace argument, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving loops
  * and harnesses that forbid allocation.  It computes exactly what
- * attr_project computes (same kernels, same bits) and makes no allocating
+ * attr_project computes (same kernels and bits; where the array holds the
+ * partials of the general projection kernel only, that kernel's bits, as
+ * attr_project gives with a workspace of its least size) and makes no allocating
  * call: its scratch is a static device array of ATTR_PROJECT_NOALLOC_SCRATCH
  * bytes, one per GPU, created when the library's code first runs on that
  * GPU and held until the process ends.  Every call on a GPU shares that
  * GPU's array, so calls that overlap on one GPU (different streams or host
  * threads without ordering) race and give undefined results; order them.
- * A call whose workspace would exceed the array (attr_project_workspace_size
- * above ATTR_PROJECT_NOALLOC_SCRATCH) returns ATTR_ERR_WORKSPACE and
+ * A call whose least workspace (the bytes below which attr_project returns
+ * ATTR_ERR_WORKSPACE) exceeds ATTR_PROJECT_NOALLOC_SCRATCH returns ATTR_ERR_WORKSPACE and
  * enqueues nothing.  Arguments and other errors as attr_project.
  */
 #define ATTR_PROJECT_NOALLOC_SCRATCH (64ull << 20)

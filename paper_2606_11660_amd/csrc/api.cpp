@@ -81,10 +81,10 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   // work per token (the row elements they read), largest first, so that the
   // one main launch starts the longest items first and ends on the
   // shortest; a group's members take consecutive slots.
-  // (three members at k = 64 would need more than 256 VGPRs: two waves per
-  // SIMD no longer fit, so groups stop at two there)
-  // (per-token blocks keep one module per item: their row-writing code would
-  // pass 256 VGPRs with two or three)
+  // (three members at k = 64 would need more than the 512 registers of a wave
+  // that has its SIMD alone, so groups stop at two there; per-token blocks keep
+  // one module per item: at k = 16 their row-writing code would pass the 256 of
+  // two waves)
   const size_t gmax = tok ? 1 : (nk >= 4 ? 2 : (size_t)attr::kProjGroupMax);
   std::vector<std::vector<int>> groups;
   std::map<std::tuple<const void*, int64_t, int64_t>, size_t> open;

@@ -23,6 +23,8 @@
 //    as one fp32 k x k partial per item; a second kernel sums the chunks of
 //    each (module, example) in chunk order into the output row
 //    (deterministic, no atomics).
+//  * Calls with few items, and fp32 at k = 32 and 64, take project_few_kernel,
+//    which splits the contraction over the four waves instead of the tokens.
 #include <mutex>
 #include <type_traits>
 
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(1024) void project_worklist_kernel(const int32_t* _
 // first), then chunk, then example, so the dispatcher hands out the most
 // expensive items first and the cheapest fill the tail of the one launch.
 // The group size is read from the group table and dispatched at run time
-// (uniform per workgroup); every size fits two waves per SIMD.
+// (uniform per workgroup); every size fits Tiles<NK>::WPS waves per SIMD.
 template <bool BF16, int NK, bool TOK>
 __global__ __launch_bounds__(256, Tiles<NK>::WPS) void project_main_kernel(
     const ProjTab* __restrict__ tab, const ProjGroup* __restrict__ gtab, int n_groups,
@@ -543,8 +545,8 @@ __global__ __launch_bounds__(256, Tiles<NK>::WPS) void project_main_kernel(
 
   __shared__ i32x4 xpose[4 * TT * 128];
   __shared__ float red[3 * KK];
-  // groups of three at k = 64 and grouped per-token blocks would pass 256
-  // VGPRs; the host never forms them
+  // groups of three at k = 64 and grouped per-token blocks would pass the
+  // registers; the host never forms them
   constexpr bool m2 = !TOK;
   constexpr bool m3 = !TOK && NK < 4;
   if (m3 && gr.ms == 3)
@@ -927,6 +929,8 @@ ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64_t slot
   ProjFewPlan P{};
   constexpr int64_t kCus = 256;
   const int64_t ct = project_chunk_tokens(nk);
+  // (in double: the workspace query takes any count)
+  if ((double)n_slots * (double)((T + 63) / 64) * (double)n_ex > (double)(1 << 24)) return P;
   if (bf16 || nk == 1) {
     // tokens an example costs; of ragged ones about 0.56 T are valid (lengths
     // even over T / 8 .. T), with half a chunk lost at the end.  At k = 16 a

@@ -4,8 +4,8 @@
 // rowscale: y = unit_normalise(m .* x) cast to the store dtype (the
 // "processing" step of section "Attribution Pipelines": unit normalisation
 // and the diagonal preconditioner; grad-cosine in the method-family table).
-// One workgroup per row; the row stays in registers between the norm and
-// the write, so X is read once and Y written once (HBM-bound).
+// One workgroup per row or two rows; they stay in registers between the norm
+// and the write, so X is read once and Y written once (HBM-bound).
 //
 // colsumsq: h_j += sum_i x_ij^2, the diagonal of the second moment G^T G.
 // Column blocks x row panels; fp32 sums over 8-row groups are added into an
