@@ -32,12 +32,6 @@ __device__ inline void load8<_Float16>(const _Float16* p, float (&v)[8]) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
 }
-template <>
-__device__ inline void load8<__bf16>(const __bf16* p, float (&v)[8]) {
-  const bf16x8 a = *(const bf16x8*)p;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
-}
 
 // Streaming (non-temporal) load of a row chunk read exactly once.
 template <typename T>
@@ -54,13 +48,6 @@ __device__ inline void load8_nt<_Float16>(const _Float16* p, float (&v)[8]) {
   const f16x8 a = __builtin_nontemporal_load((const f16x8*)p);
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
-}
-template <>
-__device__ inline void load8_nt<__bf16>(const __bf16* p, float (&v)[8]) {
-  const i32x4 a = __builtin_nontemporal_load((const i32x4*)p);
-  const bf16x8 b = __builtin_bit_cast(bf16x8, a);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = (float)b[e];
 }
 
 template <typename T>
