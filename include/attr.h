@@ -152,9 +152,8 @@ attr_status attr_project_tokens(const attr_module* mods, int32_t n_mods, attr_dt
 /* attr_project without a workspace argument, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving loops
  * and harnesses that forbid allocation.  It computes exactly what
- * attr_project computes (same kernels and bits; where the array holds the
- * partials of the general projection kernel only, that kernel's bits, as
- * attr_project gives with a workspace of its least size) and makes no allocating
+ * attr_project computes (same kernels, same bits: the chunks of a call whose
+ * partials pass the array come in several rounds) and makes no allocating
  * call: its scratch is a static device array of ATTR_PROJECT_NOALLOC_SCRATCH
  * bytes, one per GPU, created when the library's code first runs on that
  * GPU and held until the process ends.  Every call on a GPU shares that

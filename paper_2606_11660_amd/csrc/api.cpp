@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "project_plan.h"
 #include "syrk_plan.h"
 
 namespace {
@@ -61,7 +62,6 @@ bool overlap(Span a, Span b) { return a.lo < b.hi && b.lo < a.hi; }
 struct ProjLayout {
   size_t off_tab, off_gtab, off_wl, off_pk, off_part, total;
   attr::ProjFewPlan few;  // ct = 0: the general kernel
-  size_t few_total;       // bytes of the few-item plan (its partials at off_part)
   size_t query;           // bytes that the workspace query returns
   std::vector<int> order;       // slot -> module index
   std::vector<size_t> pk_off;   // per slot, relative to off_pk
@@ -116,8 +116,7 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
       L.lead_ms.push_back(u == 0 ? (int)gm.size() : 0);
     }
   }
-  const int CT = attr::project_chunk_tokens(nk);
-  L.n_chunks = (int)((T + CT - 1) / CT);
+  L.n_chunks = (int)((T + attr::kProjectChunk - 1) / attr::kProjectChunk);
   L.off_tab = 0;
   size_t off = align_up(sizeof(attr::ProjTab) * (size_t)n_mods);
   L.off_gtab = off;
@@ -149,10 +148,10 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   L.query = L.total;
   for (const bool r : {!ragged, ragged}) {
     L.few = attr::plan_project_few(eb == 2, nk, group_cost, slot_cost, cost(groups[0]), n_mods, n_ex, T, r);
-    L.few_total = L.off_part;
+    size_t few_total = L.off_part;  // the few-item plan's partials are there too
     if (L.few.ct && L.few.n_chunks > 1 && !tok)
-      L.few_total += align_up((size_t)n_mods * (size_t)L.few.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
-    L.query = std::max(L.query, L.few_total);
+      few_total += align_up((size_t)n_mods * (size_t)L.few.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
+    L.query = std::max(L.query, few_total);
   }
   return L;
 }
@@ -267,6 +266,13 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
     if (nblk > (1ll << 24))
       return fail(ATTR_ERR_UNSUPPORTED, "attr_project: %lld work items exceed one launch; split the batch",
                   (long long)nblk);
+    // A workspace below the queried size holds the partials of some of the
+    // few-item plan's chunks: they come in rounds, and the bits are the same.
+    const bool few_parts = !tok && L.few.n_chunks > 1;
+    const int round = attr::project_few_round(L.few, ws_bytes - L.off_part,
+                                              few_parts ? (size_t)n_mods * (size_t)n_examples * (size_t)k * k * 4 : 0);
+    if (L.few.ct && round < 1)
+      return fail(ATTR_ERR_WORKSPACE, "attr_project: internal: no room for the partials of a chunk");
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(ws);
     attr::ProjTab* tab = reinterpret_cast<attr::ProjTab*>(base + L.off_tab);
@@ -302,30 +308,32 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
       if (e != hipSuccess) return device_fail(e, "attr_project pack launch");
     }
     hipError_t e;
-    int n_chunks = L.n_chunks, ct = attr::project_chunk_tokens(nk);
-    bool reduce = !tok;
-    // a workspace sized for the general path alone takes the general path
-    if (L.few.ct && ws_bytes >= L.few_total) {
-      n_chunks = L.few.n_chunks;
-      ct = L.few.ct;
-      reduce = !tok && n_chunks > 1;
-      e = attr::launch_project_few(bf16, nk, L.few, tab, n_mods, n_examples, T, row_offset, length,
-                                   reduce ? part : out, tok, ldo, n_rows, s);
-    } else {
-      int32_t* wl_perm = nullptr;
-      int32_t* wl_off = nullptr;
-      if (attr::project_uses_worklist(length, n_examples, L.n_chunks)) {
-        wl_perm = reinterpret_cast<int32_t*>(base + L.off_wl);
-        wl_off = reinterpret_cast<int32_t*>(base + L.off_wl + align_up(4 * (size_t)n_examples));
+    if (L.few.ct) {
+      for (int c0 = 0; c0 < L.few.n_chunks; c0 += round) {
+        const int nc = std::min(round, L.few.n_chunks - c0);
+        e = attr::launch_project_few(bf16, nk, L.few, c0, nc, tab, n_mods, n_examples, T, row_offset, length,
+                                     few_parts ? part : out, tok, ldo, n_rows, s);
+        if (e != hipSuccess) return device_fail(e, "attr_project main launch");
+        if (!few_parts) continue;
+        e = attr::launch_project_reduce(nk, L.few.ct, c0, nc, tab, n_mods, n_examples, T, length, part, out,
+                                        ldo, s);
+        if (e != hipSuccess) return device_fail(e, "attr_project reduce launch");
       }
-      e = attr::launch_project_main(bf16, nk, tab, gtab, L.n_groups, L.n_chunks, n_examples, T,
-                                    row_offset, length, wl_perm, wl_off, tok ? out : part, s, tok, ldo,
-                                    n_rows);
+      return ATTR_OK;
     }
+    int32_t* wl_perm = nullptr;
+    int32_t* wl_off = nullptr;
+    if (attr::project_uses_worklist(length, n_examples, L.n_chunks)) {
+      wl_perm = reinterpret_cast<int32_t*>(base + L.off_wl);
+      wl_off = reinterpret_cast<int32_t*>(base + L.off_wl + align_up(4 * (size_t)n_examples));
+    }
+    e = attr::launch_project_main(bf16, nk, tab, gtab, L.n_groups, L.n_chunks, n_examples, T,
+                                  row_offset, length, wl_perm, wl_off, tok ? out : part, s, tok, ldo,
+                                  n_rows);
     if (e != hipSuccess) return device_fail(e, "attr_project main launch");
-    if (!reduce) return ATTR_OK;
-    e = attr::launch_project_reduce(nk, ct, tab, n_mods, n_chunks, n_examples, T, length, part, out, ldo,
-                                    s);
+    if (tok) return ATTR_OK;
+    e = attr::launch_project_reduce(nk, attr::kProjectChunk, 0, L.n_chunks, tab, n_mods, n_examples, T, length,
+                                    part, out, ldo, s);
     if (e != hipSuccess) return device_fail(e, "attr_project reduce launch");
     return ATTR_OK;
   } catch (const std::exception& ex) {

@@ -53,9 +53,8 @@ struct PackArgs {
   int32_t slot0;
 };
 
-// Tokens handled by one workgroup of the projection for fragment width nk
-// (k = 16 * nk).
-int project_chunk_tokens(int nk);
+// Tokens handled by one workgroup of the general projection kernel.
+constexpr int kProjectChunk = 256;
 // Bytes of packed S and R for one module.
 size_t project_packed_bytes(int64_t d_in, int64_t d_out, int k, int elem_bytes);
 
@@ -90,25 +89,23 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
                                float* partial, hipStream_t s, bool tok = false, int64_t ldo = 0,
                                int64_t n_rows = 0);
 // Calls with few items: chunks of ct tokens, the contraction split over the
-// waves of a workgroup (ct = 0: the call takes the general kernel).
+// waves of a workgroup (ct = 0: the call takes the general kernel).  The rule
+// is plan_project_few in project_plan.h (host only).
 struct ProjFewPlan {
   int ct, n_chunks;
 };
-// group_cost, slot_cost: widths of the rows read per token, with a counted once
-// per group or once per module; longest: the largest group's; ragged: lengths
-// are given.
-ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64_t slot_cost, int64_t longest,
-                             int64_t n_slots, int64_t n_ex, int64_t T, bool ragged);
-// dst: the output (tok, or a single chunk per example) or the partials
-// [slot][chunk][example][k k].
-hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, const ProjTab* tab, int n_slots,
-                              int64_t n_ex, int64_t T, const int64_t* row_offset, const int32_t* length,
-                              float* dst, bool tok, int64_t ldo, int64_t n_rows, hipStream_t s);
-// CT: tokens per chunk
-hipError_t launch_project_reduce(int nk, int CT, const ProjTab* tab, int n_slots, int n_chunks,
-                                 int64_t n_ex, int64_t T, const int32_t* length,
-                                 const float* partial, float* out, int64_t ldo,
-                                 hipStream_t s);
+// Chunks [c0, c0 + nc) of every (slot, example).  dst: the output (tok, or a
+// single chunk per example) or the partials [slot][chunk - c0][example][k k].
+hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, int c0, int nc, const ProjTab* tab,
+                              int n_slots, int64_t n_ex, int64_t T, const int64_t* row_offset,
+                              const int32_t* length, float* dst, bool tok, int64_t ldo, int64_t n_rows,
+                              hipStream_t s);
+// Adds the partials of chunks [c0, c0 + nc) (CT tokens each) to the rows of the
+// chunks before, in chunk order: the same bits whether the chunks of a call come
+// in one round or in several.
+hipError_t launch_project_reduce(int nk, int CT, int c0, int nc, const ProjTab* tab, int n_slots,
+                                 int64_t n_ex, int64_t T, const int32_t* length, const float* partial,
+                                 float* out, int64_t ldo, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // row-wise preconditioning / normalisation (NONE and DIAG)

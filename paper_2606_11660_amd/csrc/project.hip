@@ -30,6 +30,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "project_plan.h"
 
 namespace attr {
 namespace {
@@ -69,6 +70,7 @@ struct Tiles {
   static constexpr int TT = 4;
   static constexpr int PD = 3;
   static constexpr int WPS = NK == 1 ? 2 : 1;
+  static_assert(64 * TT == kProjectChunk, "four waves of TT tiles");
 };
 
 // bf16 bit pattern <-> float (bf16 is the upper half of an fp32 pattern);
@@ -597,10 +599,11 @@ struct FewTiles {
 };
 
 // direct: a single chunk per example, whose block goes to its place in the
-// output (dst, row stride ldo) instead of to a partial.
+// output (dst, row stride ldo) instead of to a partial.  The launch takes the
+// n_chunks chunks from c0.
 template <bool BF16, int NK, int TT, bool TOK>
 __global__ __launch_bounds__(256, 2) void project_few_kernel(
-    const ProjTab* __restrict__ tab, int n_chunks, int64_t n_ex, int64_t T,
+    const ProjTab* __restrict__ tab, int c0, int n_chunks, int64_t n_ex, int64_t T,
     const int64_t* __restrict__ row_offset, const int32_t* __restrict__ length,
     float* __restrict__ dst, int64_t ldo, int64_t n_rows, int direct) {
   using E_t = ElemT<BF16>;
@@ -622,7 +625,7 @@ __global__ __launch_bounds__(256, 2) void project_few_kernel(
   const uint32_t i = (blk - rest * nex + (rest + (uint32_t)s) % nex) % nex;
   int64_t len = length ? (int64_t)length[i] : T;
   len = len < 0 ? 0 : (len > T ? T : len);
-  const int64_t t0 = (int64_t)c * CT;
+  const int64_t t0 = (int64_t)(c0 + c) * CT;
   const ProjTab md = tab[s];
   if (t0 >= len) {  // uniform
     if (!TOK && direct)
@@ -797,11 +800,12 @@ __global__ __launch_bounds__(256, 2) void project_few_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// reduce: out[i, out_col + r*k + c] = sum over chunks of the item partials.
+// reduce: out[i, out_col + r*k + c] = sum over chunks of the item partials; the
+// chunks from c0 > 0 on are added to what the chunks before them left in out.
 // ---------------------------------------------------------------------------
 template <int NK>
 __global__ __launch_bounds__(256) void project_reduce_kernel(
-    const ProjTab* __restrict__ tab, int n_chunks, int64_t n_ex, int64_t T, int CT,
+    const ProjTab* __restrict__ tab, int c0, int n_chunks, int64_t n_ex, int64_t T, int CT,
     const int32_t* __restrict__ length, const float* __restrict__ partial,
     float* __restrict__ out, int64_t ldo) {
   constexpr int KK = 256 * NK * NK;
@@ -809,12 +813,15 @@ __global__ __launch_bounds__(256) void project_reduce_kernel(
   const int s = (int)(blockIdx.x / n_ex);
   int64_t len = length ? (int64_t)length[i] : T;
   len = len < 0 ? 0 : (len > T ? T : len);
-  const int nck = (int)((len + CT - 1) / CT);
-  const int64_t out_col = tab[s].out_col;
+  int nck = (int)((len + CT - 1) / CT) - c0;
+  nck = nck > n_chunks ? n_chunks : nck;
+  if (c0 > 0 && nck <= 0) return;
+  float* orow = out + i * ldo + tab[s].out_col;
   for (int e = threadIdx.x; e < KK; e += blockDim.x) {
-    float v = 0.f;
+    float* o = orow + block_pos<NK>(e);
+    float v = c0 > 0 ? *o : 0.f;
     for (int c = 0; c < nck; ++c) v += partial[((((int64_t)s * n_chunks + c) * n_ex) + i) * KK + e];
-    out[i * ldo + out_col + block_pos<NK>(e)] = v;
+    *o = v;
   }
 }
 
@@ -836,11 +843,6 @@ hipError_t project_scratch(void** ptr) {
   }
   *ptr = g_scratch_ptr[dev];
   return hipSuccess;
-}
-
-int project_chunk_tokens(int nk) {
-  (void)nk;
-  return 64 * Tiles<1>::TT;  // the same for every width
 }
 
 size_t project_packed_bytes(int64_t d_in, int64_t d_out, int k, int elem_bytes) {
@@ -875,7 +877,7 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
   if (nblk == 0) return hipSuccess;
   if (wl_perm) {
     hipLaunchKernelGGL(project_worklist_kernel, dim3(1), dim3(1024), 0, s, length, n_ex, T,
-                       project_chunk_tokens(nk), n_chunks, wl_perm, wl_off);
+                       kProjectChunk, n_chunks, wl_perm, wl_off);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -901,75 +903,19 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
   return hipGetLastError();
 }
 
-// Rates of the two kernels in elements of token rows (a and g widths times
-// tokens) per us and CU, and the latency of the longest item's K-groups that
-// the split saves, in us per group; from 12-layer GPT-2-shaped and 2- to
-// 6-layer 1B-shaped calls of 16 to 16384 tokens, even and ragged.
-struct FewRates {
-  double general, few, group;
-};
-static FewRates few_rates(bool bf16, int nk) {
-  if (bf16) return nk == 1 ? FewRates{14000, 12800, 0.3} : nk == 2 ? FewRates{12000, 11250, 0.15} : FewRates{10500, 8000, 0.08};
-  return FewRates{7000, 6700, 0.3};
-}
-
-// The general kernel reads a once per group and runs a little faster where
-// there are items enough; the split one has a chain a quarter as long and
-// wastes at most 63 tokens of a chunk.  Both times are modelled and the lower
-// one is taken.  fp32 at k = 32 and 64 is bound by the matrix cores and always
-// takes the split kernel, which computes no tile without tokens (16 ragged
-// GPT-2-shaped examples of up to 512 tokens: 682 -> 609 us at k = 32, 1224 ->
-// 926 at k = 64; 16384 tokens: 1916 -> 1752 and 3552 -> 2796).  bf16, k = 16,
-// 12 GPT-2-shaped layers, general / split: one example of 16 tokens 46 / 16
-// us, 389 tokens 86 / 46, 1024 tokens 99 / 75, 8 x 512 tokens 228 / 209, 16 x
-// 512 397 / 392, 32 x 512 743 / 759; 2 1B-shaped layers: 149 tokens 229 / 29,
-// 4 x 1343 297 / 187, 8 x 2048 506 / 538.
-ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64_t slot_cost, int64_t longest,
-                             int64_t n_slots, int64_t n_ex, int64_t T, bool ragged) {
-  ProjFewPlan P{};
-  constexpr int64_t kCus = 256;
-  const int64_t ct = project_chunk_tokens(nk);
-  // (in double: the workspace query takes any count)
-  if ((double)n_slots * (double)((T + 63) / 64) * (double)n_ex > (double)(1 << 24)) return P;
-  if (bf16 || nk == 1) {
-    // tokens an example costs; of ragged ones about 0.56 T are valid (lengths
-    // even over T / 8 .. T), with half a chunk lost at the end.  At k = 16 a
-    // chunk's tokens are spread over the waves and only the loads cost.
-    const double valid = ragged ? 0.56 * (double)T : (double)T;
-    auto cost_tokens = [&](int64_t c) {
-      if (nk == 1) return valid + 32.0;
-      return ragged && T > c ? valid + 0.5 * (double)c : (double)((T + c - 1) / c * c);
-    };
-    const FewRates r = few_rates(bf16, nk);
-    const double tg = (double)group_cost * cost_tokens(ct) * (double)n_ex / (double)kCus / r.general;
-    const double tf = (double)slot_cost * cost_tokens(64) * (double)n_ex / (double)kCus / r.few;
-    const double groups = (double)longest * (bf16 ? 2 : 4) / 128.0;
-    if (!(tf < tg + r.group * groups)) return P;
-  }
-  // One token tile per workgroup where even then few workgroups exist and the
-  // modules are wide: R and S are read four times as often (one 149-token
-  // example of 2 1B-shaped layers: 40 -> 29 us; of 128 tokens over 12
-  // GPT-2-shaped layers: 28 -> 32 us).
-  const int tt = n_slots * ((T + 15) / 16) * n_ex * 24 <= slot_cost / n_slots ? 1 : 4;
-  const int64_t chunks = (T + 16 * tt - 1) / (16 * tt);
-  if (n_slots * chunks * n_ex > ((int64_t)1 << 24)) return P;
-  P.ct = 16 * tt;
-  P.n_chunks = (int)chunks;
-  return P;
-}
-
-hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, const ProjTab* tab, int n_slots,
-                              int64_t n_ex, int64_t T, const int64_t* row_offset, const int32_t* length,
-                              float* dst, bool tok, int64_t ldo, int64_t n_rows, hipStream_t s) {
-  dim3 grid((unsigned)((int64_t)n_slots * P.n_chunks * n_ex)), block(256);
+hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, int c0, int nc, const ProjTab* tab,
+                              int n_slots, int64_t n_ex, int64_t T, const int64_t* row_offset,
+                              const int32_t* length, float* dst, bool tok, int64_t ldo, int64_t n_rows,
+                              hipStream_t s) {
+  dim3 grid((unsigned)((int64_t)n_slots * nc * n_ex)), block(256);
   const int direct = !tok && P.n_chunks == 1;
 #define ATTR_FEW(B, N, TT)                                                                            \
   if (nk == N && P.ct == 16 * TT) {                                                                   \
     if (tok)                                                                                          \
-      hipLaunchKernelGGL((project_few_kernel<B, N, TT, true>), grid, block, 0, s, tab, P.n_chunks, n_ex, \
+      hipLaunchKernelGGL((project_few_kernel<B, N, TT, true>), grid, block, 0, s, tab, c0, nc, n_ex, \
                          T, row_offset, length, dst, ldo, n_rows, direct);                            \
     else                                                                                              \
-      hipLaunchKernelGGL((project_few_kernel<B, N, TT, false>), grid, block, 0, s, tab, P.n_chunks, n_ex, \
+      hipLaunchKernelGGL((project_few_kernel<B, N, TT, false>), grid, block, 0, s, tab, c0, nc, n_ex, \
                          T, row_offset, length, dst, ldo, n_rows, direct);                            \
   }
 #define ATTR_FEW_NK(B) \
@@ -984,13 +930,12 @@ hipError_t launch_project_few(bool bf16, int nk, const ProjFewPlan& P, const Pro
   return hipGetLastError();
 }
 
-hipError_t launch_project_reduce(int nk, int CT, const ProjTab* tab, int n_slots, int n_chunks,
-                                 int64_t n_ex, int64_t T, const int32_t* length,
-                                 const float* partial, float* out, int64_t ldo,
-                                 hipStream_t s) {
+hipError_t launch_project_reduce(int nk, int CT, int c0, int nc, const ProjTab* tab, int n_slots,
+                                 int64_t n_ex, int64_t T, const int32_t* length, const float* partial,
+                                 float* out, int64_t ldo, hipStream_t s) {
   dim3 grid((unsigned)((int64_t)n_slots * n_ex)), block(256);
 #define ATTR_RED(N)                                                                          \
-  hipLaunchKernelGGL((project_reduce_kernel<N>), grid, block, 0, s, tab, n_chunks, n_ex, T, CT, \
+  hipLaunchKernelGGL((project_reduce_kernel<N>), grid, block, 0, s, tab, c0, nc, n_ex, T, CT, \
                      length, partial, out, ldo)
   if (nk == 1) ATTR_RED(1);
   else if (nk == 2) ATTR_RED(2);
