@@ -149,8 +149,8 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   for (const bool r : {!ragged, ragged}) {
     L.few = attr::plan_project_few(eb == 2, nk, group_cost, slot_cost, cost(groups[0]), n_mods, n_ex, T, r);
     size_t few_total = L.off_part;  // the few-item plan's partials are there too
-    if (L.few.ct && L.few.n_chunks > 1 && !tok)
-      few_total += align_up((size_t)n_mods * (size_t)L.few.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
+    if (L.few.ct && L.few.n_chunks > 1 && !tok && n_ex > 0)
+      few_total += align_up(attr::project_few_query(L.few, (size_t)n_mods * (size_t)n_ex * (size_t)k * k * 4));
     L.query = std::max(L.query, few_total);
   }
   return L;
@@ -266,13 +266,15 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
     if (nblk > (1ll << 24))
       return fail(ATTR_ERR_UNSUPPORTED, "attr_project: %lld work items exceed one launch; split the batch",
                   (long long)nblk);
-    // A workspace below the queried size holds the partials of some of the
-    // few-item plan's chunks: they come in rounds, and the bits are the same.
+    // The few-item plan's chunks come in rounds of as many as a launch takes and
+    // a workspace below the queried size holds partials for: the same bits.
     const bool few_parts = !tok && L.few.n_chunks > 1;
-    const int round = attr::project_few_round(L.few, ws_bytes - L.off_part,
-                                              few_parts ? (size_t)n_mods * (size_t)n_examples * (size_t)k * k * 4 : 0);
-    if (L.few.ct && round < 1)
-      return fail(ATTR_ERR_WORKSPACE, "attr_project: internal: no room for the partials of a chunk");
+    const int64_t items = (int64_t)n_mods * n_examples;
+    const int round = attr::project_few_round(L.few, items, ws_bytes - L.off_part,
+                                              few_parts ? (size_t)items * (size_t)k * k * 4 : 0);
+    if (L.few.ct ? round < 1 : std::max(items, (int64_t)L.n_groups * L.n_chunks * n_examples) > attr::kProjectMaxBlocks)
+      return fail(ATTR_ERR_UNSUPPORTED, "attr_project: %lld modules x examples exceed one launch; split the batch",
+                  (long long)items);
     hipStream_t s = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(ws);
     attr::ProjTab* tab = reinterpret_cast<attr::ProjTab*>(base + L.off_tab);

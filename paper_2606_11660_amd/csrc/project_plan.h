@@ -39,8 +39,7 @@ inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64
   ProjFewPlan P{};
   constexpr int64_t kCus = 256;
   const int64_t ct = kProjectChunk;
-  // (in double: the workspace query takes any count)
-  if ((double)n_slots * (double)((T + 63) / 64) * (double)n_ex > (double)(1 << 24)) return P;
+  if (T > ((int64_t)1 << 24)) return P;  // (refused; the workspace query takes any length)
   if (bf16 || nk == 1) {
     // tokens an example costs; of ragged ones about 0.56 T are valid (lengths
     // even over T / 8 .. T), with half a chunk lost at the end.  At k = 16 a
@@ -60,22 +59,34 @@ inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64
   // modules are wide: R and S are read four times as often (one 149-token
   // example of 2 1B-shaped layers: 40 -> 29 us; of 128 tokens over 12
   // GPT-2-shaped layers: 28 -> 32 us).
-  const int tt = n_slots * ((T + 15) / 16) * n_ex * 24 <= slot_cost / n_slots ? 1 : 4;
-  const int64_t chunks = (T + 16 * tt - 1) / (16 * tt);
-  if (n_slots * chunks * n_ex > ((int64_t)1 << 24)) return P;
-  P.ct = 16 * tt;
-  P.n_chunks = (int)chunks;
+  // (in double: the workspace query takes any count)
+  const double blocks = (double)n_slots * (double)((T + 15) / 16) * (double)n_ex;
+  P.ct = blocks * 24 <= (double)(slot_cost / n_slots) ? 16 : 64;
+  P.n_chunks = (int)((T + P.ct - 1) / P.ct);
   return P;
 }
 
+// A launch has fewer than 2^32 threads: fewer than 2^24 workgroups of 256.
+constexpr int64_t kProjectMaxBlocks = ((int64_t)1 << 24) - 1;
 
-// Chunks per round of the split kernel: as many as the partials have room for
-// (room bytes; part_bytes a chunk of all slots and examples; 0: no partials).
-// The least workspace that a call accepts holds the general kernel's partials,
-// one chunk of 256 tokens at least, so it holds one of these.
-inline int project_few_round(const ProjFewPlan& P, size_t room, size_t part_bytes) {
-  const size_t fit = part_bytes ? room / part_bytes : (size_t)P.n_chunks;
-  return (int)std::min<size_t>(fit, (size_t)P.n_chunks);
+// The query asks for the partials of all chunks up to kProjectRoundBytes, beyond
+// that for as many chunks as those bytes hold: a round of 256 MiB is at least
+// 16384 workgroups.
+constexpr size_t kProjectRoundBytes = (size_t)256 << 20;
+inline size_t project_few_query(const ProjFewPlan& P, size_t part_bytes) {
+  if (!part_bytes) return 0;  // (a count past 64 bits: the call is refused)
+  const size_t fit = std::max<size_t>(1, kProjectRoundBytes / part_bytes);
+  return part_bytes * std::min<size_t>(fit, (size_t)P.n_chunks);
+}
+
+// Chunks per round of the split kernel: as many as one launch takes (items:
+// slots times examples) and the partials have room for (room bytes; part_bytes a
+// chunk of all items; 0: no partials).  The least workspace that a call accepts
+// holds the general kernel's partials, one chunk of 256 tokens at least, so it
+// holds one of these.
+inline int project_few_round(const ProjFewPlan& P, int64_t items, size_t room, size_t part_bytes) {
+  const int64_t fit = part_bytes ? (int64_t)(room / part_bytes) : P.n_chunks;
+  return (int)std::min<int64_t>({fit, kProjectMaxBlocks / items, P.n_chunks});
 }
 
 }  // namespace attr
