@@ -104,7 +104,9 @@ typedef struct {
  * bit pattern including NaN.  Modules that pass the same a pointer with the
  * same lda and d_in (the q/k/v or gate/up projections of one layer) have
  * their shared rows read once for up to three of them (two at k = 64); the
- * results are the same bits as with separate copies of a.
+ * results are the same bits as with separate copies of a.  The order of the
+ * fp32 sums, and so the last bits of a row, depend on the call (the modules'
+ * widths, n_examples, T and whether lengths are given), not on the workspace.
  *
  *   mods       (host) [n_mods] module descriptors; 1 <= n_mods <= 4096
  *   in_dtype   ATTR_BF16 (bf16 MFMA, fp32 accumulate) or ATTR_F32 (fp32 MFMA)

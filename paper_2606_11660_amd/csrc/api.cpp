@@ -140,14 +140,16 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   // group table fits what the query (which does not know the call) returns
   if (!tok) off += align_up((size_t)n_mods * (size_t)L.n_chunks * (size_t)n_ex * (size_t)k * k * 4);
   L.total = off;
-  int64_t group_cost = 0, slot_cost = 0;
-  for (const auto& gm : groups) group_cost += cost(gm);
-  for (int x = 0; x < n_mods; ++x) slot_cost += mods[x].d_in + mods[x].d_out;
+  int64_t slot_cost = 0, longest = 0;
+  for (int x = 0; x < n_mods; ++x) {
+    slot_cost += mods[x].d_in + mods[x].d_out;
+    longest = std::max(longest, mods[x].d_in + mods[x].d_out);
+  }
   // the plan of this call, and the bytes of the larger of the plans with and
   // without lengths: the query does not know which the call will have
   L.query = L.total;
   for (const bool r : {!ragged, ragged}) {
-    L.few = attr::plan_project_few(eb == 2, nk, group_cost, slot_cost, cost(groups[0]), n_mods, n_ex, T, r);
+    L.few = attr::plan_project_few(eb == 2, nk, slot_cost, longest, n_mods, n_ex, T, r);
     size_t few_total = L.off_part;  // the few-item plan's partials are there too
     if (L.few.ct && L.few.n_chunks > 1 && !tok && n_ex > 0)
       few_total += align_up(attr::project_few_query(L.few, (size_t)n_mods * (size_t)n_ex * (size_t)k * k * 4));

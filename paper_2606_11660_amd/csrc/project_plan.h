@@ -4,6 +4,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -11,49 +12,51 @@
 
 namespace attr {
 
-// Rates of the two kernels in elements of token rows (a and g widths times
-// tokens) per us and CU, and the latency of the longest item's K-groups that
-// the split saves, in us per group; from 12-layer GPT-2-shaped and 2- to
-// 6-layer 1B-shaped calls of 16 to 16384 tokens, even and ragged.
-struct FewRates {
-  double general, few, group;
+// The split kernel's rate over the general one's, and the lead that a quarter as
+// long a chain gives it, in token-elements per element of the widest module.
+struct FewRule {
+  double rate, lead;
 };
-inline FewRates few_rates(bool bf16, int nk) {
-  if (bf16) return nk == 1 ? FewRates{14000, 12800, 0.3} : nk == 2 ? FewRates{12000, 11250, 0.15} : FewRates{10500, 8000, 0.08};
-  return FewRates{7000, 6700, 0.3};
+inline FewRule few_rule(bool bf16, int nk) {
+  if (!bf16) return {0.94, 12000};
+  return nk == 1 ? FewRule{0.84, 26000} : nk == 2 ? FewRule{0.95, 6000} : FewRule{0.91, 4000};
 }
 
-// The general kernel reads a once per group and runs a little faster where
-// there are items enough; the split one has a chain a quarter as long and
-// wastes at most 63 tokens of a chunk.  Both times are modelled and the lower
-// one is taken.  fp32 at k = 32 and 64 is bound by the matrix cores and always
-// takes the split kernel, which computes no tile without tokens (16 ragged
-// GPT-2-shaped examples of up to 512 tokens: 682 -> 609 us at k = 32, 1224 ->
-// 926 at k = 64; 16384 tokens: 1916 -> 1752 and 3552 -> 2796).  bf16, k = 16,
-// 12 GPT-2-shaped layers, general / split: one example of 16 tokens 46 / 16
-// us, 389 tokens 86 / 46, 1024 tokens 99 / 75, 8 x 512 tokens 228 / 209, 16 x
-// 512 397 / 392, 32 x 512 743 / 759; 2 1B-shaped layers: 149 tokens 229 / 29,
-// 4 x 1343 297 / 187, 8 x 2048 506 / 538.
-inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t group_cost, int64_t slot_cost, int64_t longest,
-                             int64_t n_slots, int64_t n_ex, int64_t T, bool ragged) {
+// Which kernel a call takes.  The general kernel reads a once per group and runs a
+// little faster where there are items enough; the split one has a chain a quarter
+// as long and wastes at most 63 tokens of a chunk.  A chunk costs either kernel
+// its tokens and some more (64 of 256, 16 of 64: a 60-token example takes the
+// general kernel 40% of a 256-token chunk's time).  The rule sees the widths of
+// the modules but not which of them share their input rows: the two kernels add in
+// different orders, and modules that share rows give the same bits as separate
+// copies.  So the line lies between the two.  General / split in us, bf16, k = 16:
+// 2 1B-shaped layers of 8 x 2048 tokens 503 / 541 shared and 529 / 543 separate,
+// of 6 x 2048 440 / 394 and 383 / 402 (general from here on), of 4 x 2048 312 /
+// 285 and 259 / 270, of 2 x 2048 280 / 157; 12 GPT-2-shaped layers of 16 x 512 376
+// / 377, of 8 x 512 215 / 198, of 200 x 60 943 / 546, one of 389 tokens 86 / 46.
+// k = 64: 2 1B-shaped layers of 2 x 2048 404 / 328, of 4 x 2048 449 / 486.
+// Lengths are on the device and not known here: three quarters of a slot's tokens
+// are counted where they are given.  Next to the line the split kernel is far
+// ahead where they are even over T / 8 .. T (k = 32, 2 1B-shaped layers, 8 x 2048:
+// 323 / 249) and behind where nearly all are T (497 / 577).  fp32 at k = 32 and 64
+// is bound by the matrix cores and always takes the split kernel, which computes
+// no tile without tokens (16 ragged GPT-2-shaped examples of up to 512 tokens: 682
+// / 609 at k = 32, 1224 / 926 at k = 64; 16384 tokens: 1916 / 1752 and 3552 /
+// 2796).
+// slot_cost, longest: sum and maximum over the modules of d_in + d_out.
+inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t slot_cost, int64_t longest, int64_t n_slots,
+                                    int64_t n_ex, int64_t T, bool ragged) {
   ProjFewPlan P{};
-  constexpr int64_t kCus = 256;
-  const int64_t ct = kProjectChunk;
   if (T > ((int64_t)1 << 24)) return P;  // (refused; the workspace query takes any length)
   if (bf16 || nk == 1) {
-    // tokens an example costs; of ragged ones about 0.56 T are valid (lengths
-    // even over T / 8 .. T), with half a chunk lost at the end.  At k = 16 a
-    // chunk's tokens are spread over the waves and only the loads cost.
-    const double valid = ragged ? 0.56 * (double)T : (double)T;
-    auto cost_tokens = [&](int64_t c) {
-      if (nk == 1) return valid + 32.0;
-      return ragged && T > c ? valid + 0.5 * (double)c : (double)((T + c - 1) / c * c);
+    const double valid = ragged ? 0.75 * (double)T : (double)T;
+    // tokens that an example in chunks of c costs, extra ones per chunk
+    auto cost = [&](double c, double extra) {
+      return valid + extra * (ragged && (double)T > c ? valid / c + 0.5 : std::ceil((double)T / c));
     };
-    const FewRates r = few_rates(bf16, nk);
-    const double tg = (double)group_cost * cost_tokens(ct) * (double)n_ex / (double)kCus / r.general;
-    const double tf = (double)slot_cost * cost_tokens(64) * (double)n_ex / (double)kCus / r.few;
-    const double groups = (double)longest * (bf16 ? 2 : 4) / 128.0;
-    if (!(tf < tg + r.group * groups)) return P;
+    const FewRule r = few_rule(bf16, nk);
+    const double behind = cost(64, 16) / r.rate - cost(kProjectChunk, 64);
+    if (!((double)slot_cost * (double)n_ex * behind < r.lead * (double)longest)) return P;
   }
   // One token tile per workgroup where even then few workgroups exist and the
   // modules are wide: R and S are read four times as often (one 149-token
