@@ -83,8 +83,7 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   // shortest; a group's members take consecutive slots.
   // (three members at k = 64 would need more than the 512 registers of a wave
   // that has its SIMD alone, so groups stop at two there; per-token blocks keep
-  // one module per item: at k = 16 their row-writing code would pass the 256 of
-  // two waves)
+  // one module per item: their row-writing code would pass the 256 of two waves)
   const size_t gmax = tok ? 1 : (nk >= 4 ? 2 : (size_t)attr::kProjGroupMax);
   std::vector<std::vector<int>> groups;
   std::map<std::tuple<const void*, int64_t, int64_t>, size_t> open;
@@ -116,7 +115,8 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
       L.lead_ms.push_back(u == 0 ? (int)gm.size() : 0);
     }
   }
-  L.n_chunks = (int)((T + attr::kProjectChunk - 1) / attr::kProjectChunk);
+  const int CT = attr::project_chunk_tokens(nk, tok);
+  L.n_chunks = (int)((T + CT - 1) / CT);
   L.off_tab = 0;
   size_t off = align_up(sizeof(attr::ProjTab) * (size_t)n_mods);
   L.off_gtab = off;
@@ -336,7 +336,7 @@ static attr_status project_impl(const attr_module* mods, int32_t n_mods, attr_dt
                                   n_rows);
     if (e != hipSuccess) return device_fail(e, "attr_project main launch");
     if (tok) return ATTR_OK;
-    e = attr::launch_project_reduce(nk, attr::kProjectChunk, 0, L.n_chunks, tab, n_mods, n_examples, T, length,
+    e = attr::launch_project_reduce(nk, attr::project_chunk_tokens(nk, false), 0, L.n_chunks, tab, n_mods, n_examples, T, length,
                                     part, out, ldo, s);
     if (e != hipSuccess) return device_fail(e, "attr_project reduce launch");
     return ATTR_OK;

@@ -53,8 +53,9 @@ struct PackArgs {
   int32_t slot0;
 };
 
-// Tokens handled by one workgroup of the general projection kernel.
-constexpr int kProjectChunk = 256;
+// Tokens handled by one workgroup of the general projection kernel for fragment
+// width nk (k = 16 nk); per-token calls (tok) take fewer at k = 32 and 64.
+constexpr int project_chunk_tokens(int nk, bool tok) { return tok ? 256 / nk : 256; }
 // Bytes of packed S and R for one module.
 size_t project_packed_bytes(int64_t d_in, int64_t d_out, int k, int elem_bytes);
 

@@ -59,18 +59,21 @@ struct ElemT<false> {
 };
 
 // Token tiles (16 tokens) per wave, load steps kept in flight and waves per
-// SIMD, per fragment width NK (k = 16 NK).  Every wave reads the fragments of R
+// SIMD, per fragment width NK (k = 16 NK) and kind of call.  Every wave reads the fragments of R
 // and S for its own tokens from L2, 32 NK bytes a K element in bf16 against
 // 32 TT of the token rows: four tiles keep that at k = 32 and 64 to half and
 // all of the rows' bytes, at one wave per SIMD (two and one tile, two waves:
 // 32 GPT-2-shaped examples x 512 tokens in bf16 890 -> 815 us at k = 32 and
-// 1540 -> 1051 us at k = 64).
-template <int NK>
+// 1540 -> 1051 us at k = 64).  Per-token calls write their blocks between the
+// items and keep two and one tile and two waves: with four and one, 4 GPT-2-shaped
+// layers of 8 x 512 tokens at k = 32 take 174 us instead of 150, 2 of 4 x 512 at k
+// = 64 168 instead of 111.
+template <int NK, bool TOK>
 struct Tiles {
-  static constexpr int TT = 4;
+  static constexpr int TT = TOK ? 4 / NK : 4;
   static constexpr int PD = 3;
-  static constexpr int WPS = NK == 1 ? 2 : 1;
-  static_assert(64 * TT == kProjectChunk, "four waves of TT tiles");
+  static constexpr int WPS = TOK || NK == 1 ? 2 : 1;
+  static_assert(64 * TT == project_chunk_tokens(NK, TOK), "four waves of TT tiles");
 };
 
 // bf16 bit pattern <-> float (bf16 is the upper half of an fp32 pattern);
@@ -318,7 +321,7 @@ __device__ inline void project_item(const ProjTab* __restrict__ tab, int s0, uin
   constexpr int EB = E_t::bytes;
   constexpr int E = 16 / EB;
   constexpr int KS = 4 * E;
-  constexpr int TT = Tiles<NK>::TT;
+  constexpr int TT = Tiles<NK, TOK>::TT;
   constexpr int TPW = 16 * TT;  // tokens per wave
   constexpr int CT = 4 * TPW;   // tokens per workgroup
   constexpr int KK = 256 * NK * NK;
@@ -354,7 +357,7 @@ __device__ inline void project_item(const ProjTab* __restrict__ tab, int s0, uin
     const i32x4* pkS[MS];
 #pragma unroll
     for (int m = 0; m < MS; ++m) pkS[m] = (const i32x4*)tab[s0 + m].pk;
-    project_side<Tag, E, NK, TT, Tiles<NK>::PD, MS>(ra, m0.lda, m0.d_in, pkS, lane, xp, At);
+    project_side<Tag, E, NK, TT, Tiles<NK, TOK>::PD, MS>(ra, m0.lda, m0.d_in, pkS, lane, xp, At);
   }
 
 #pragma unroll
@@ -374,7 +377,7 @@ __device__ inline void project_item(const ProjTab* __restrict__ tab, int s0, uin
       for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
         for (int ct = 0; ct < NK; ++ct) Gt[0][tt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-      project_side<Tag, E, NK, TT, Tiles<NK>::PD, 1>(rg, md.ldg, md.d_out, pkR, lane, xp, Gt);
+      project_side<Tag, E, NK, TT, Tiles<NK, TOK>::PD, 1>(rg, md.ldg, md.d_out, pkR, lane, xp, Gt);
 
       if constexpr (TOK) {
         // register q of the stage-1 tiles holds token 16 tt + 4 (lane / 16) +
@@ -492,15 +495,15 @@ __global__ __launch_bounds__(1024) void project_worklist_kernel(const int32_t* _
 // first), then chunk, then example, so the dispatcher hands out the most
 // expensive items first and the cheapest fill the tail of the one launch.
 // The group size is read from the group table and dispatched at run time
-// (uniform per workgroup); every size fits Tiles<NK>::WPS waves per SIMD.
+// (uniform per workgroup); every size fits Tiles::WPS waves per SIMD.
 template <bool BF16, int NK, bool TOK>
-__global__ __launch_bounds__(256, Tiles<NK>::WPS) void project_main_kernel(
+__global__ __launch_bounds__(256, (Tiles<NK, TOK>::WPS)) void project_main_kernel(
     const ProjTab* __restrict__ tab, const ProjGroup* __restrict__ gtab, int n_groups,
     int n_chunks, int64_t n_ex, int64_t T, const int64_t* __restrict__ row_offset,
     const int32_t* __restrict__ length, const int32_t* __restrict__ wl_perm,
     const int32_t* __restrict__ wl_off, float* __restrict__ partial, int64_t ldo,
     int64_t n_rows) {
-  constexpr int TT = Tiles<NK>::TT;
+  constexpr int TT = Tiles<NK, TOK>::TT;
   constexpr int CT = 4 * 16 * TT;  // tokens per workgroup
   constexpr int KK = 256 * NK * NK;
   // Work-item decode in 32-bit scalar arithmetic (the host keeps the grid
@@ -877,7 +880,7 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
   if (nblk == 0) return hipSuccess;
   if (wl_perm) {
     hipLaunchKernelGGL(project_worklist_kernel, dim3(1), dim3(1024), 0, s, length, n_ex, T,
-                       kProjectChunk, n_chunks, wl_perm, wl_off);
+                       project_chunk_tokens(nk, tok), n_chunks, wl_perm, wl_off);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

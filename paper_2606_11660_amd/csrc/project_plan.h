@@ -55,7 +55,7 @@ inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t slot_cost, int64_
       return valid + extra * (ragged && (double)T > c ? valid / c + 0.5 : std::ceil((double)T / c));
     };
     const FewRule r = few_rule(bf16, nk);
-    const double behind = cost(64, 16) / r.rate - cost(kProjectChunk, 64);
+    const double behind = cost(64, 16) / r.rate - cost(project_chunk_tokens(nk, false), 64);
     if (!((double)slot_cost * (double)n_ex * behind < r.lead * (double)longest)) return P;
   }
   // One token tile per workgroup where even then few workgroups exist and the

@@ -18,7 +18,7 @@ int main() {
           for (long long n : {1ll, 2ll, 7ll, 64ll, 1000ll, 65536ll, 1ll << 22, 1ll << 24})
             for (long long T : {1ll, 16ll, 63ll, 64ll, 65ll, 255ll, 256ll, 257ll, 2048ll, 100000ll, 1ll << 24})
               for (bool ragged : {false, true}) {
-                const long long chunks = (T + attr::kProjectChunk - 1) / attr::kProjectChunk;
+                const long long ct = attr::project_chunk_tokens(nk, false), chunks = (T + ct - 1) / ct;
                 if ((double)mods * chunks * n > (double)(1 << 24)) continue;  // the call is refused
                 if (mods * n == 1 << 24) continue;  // one launch cannot take even one chunk: refused
                 const attr::ProjFewPlan P =
