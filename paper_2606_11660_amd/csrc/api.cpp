@@ -149,7 +149,7 @@ ProjLayout project_layout(const attr_module* mods, int32_t n_mods, int eb, int64
   // without lengths: the query does not know which the call will have
   L.query = L.total;
   for (const bool r : {!ragged, ragged}) {
-    L.few = attr::plan_project_few(eb == 2, nk, slot_cost, longest, n_mods, n_ex, T, r);
+    L.few = attr::plan_project_few(eb == 2, nk, tok, slot_cost, longest, n_mods, n_ex, T, r);
     size_t few_total = L.off_part;  // the few-item plan's partials are there too
     if (L.few.ct && L.few.n_chunks > 1 && !tok && n_ex > 0)
       few_total += align_up(attr::project_few_query(L.few, (size_t)n_mods * (size_t)n_ex * (size_t)k * k * 4));

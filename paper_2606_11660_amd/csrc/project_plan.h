@@ -17,7 +17,8 @@ namespace attr {
 struct FewRule {
   double rate, lead;
 };
-inline FewRule few_rule(bool bf16, int nk) {
+inline FewRule few_rule(bool bf16, int nk, bool tok) {
+  if (tok) return nk == 1 ? FewRule{0.75, bf16 ? 28000.0 : 40000.0} : nk == 2 ? FewRule{0.79, 4000} : FewRule{0.60, 1000};
   if (!bf16) return {0.94, 12000};
   return nk == 1 ? FewRule{0.84, 26000} : nk == 2 ? FewRule{0.95, 6000} : FewRule{0.91, 4000};
 }
@@ -43,9 +44,19 @@ inline FewRule few_rule(bool bf16, int nk) {
 // no tile without tokens (16 ragged GPT-2-shaped examples of up to 512 tokens: 682
 // / 609 at k = 32, 1224 / 926 at k = 64; 16384 tokens: 1916 / 1752 and 3552 /
 // 2796).
+// Per-token calls (tok) have a rule of their own: both kernels also write k^2
+// values per token and module, which hides a part of the general one's chain.
+// bf16, k = 16: 12 GPT-2-shaped layers of 16 x 512 tokens 507 / 542, of 8 x 512
+// 296 / 296, one of 512 tokens 73 / 51; 2 1B-shaped layers of 4 x 2048 289 / 299
+// (general from here on), of 2 x 2048 186 / 151.  k = 32: 4 GPT-2-shaped layers of
+// 8 x 512 150 / 175 (general), of 4 x 512 90 / 88.  fp32, k = 16: 12 layers of 16
+// x 512 896 / 940, of 8 x 512 510 / 459 (general), of 4 x 512 272 / 238.  k = 64,
+// bf16: 2 layers of 4 x 512 111 / 139 (general), of 2 x 512 78 / 63.  fp32 at k =
+// 32 and 64 up to 6% behind at single sizes (4 layers of 8 x 512, k = 32: 233 /
+// 249), up to 70% ahead at others.
 // slot_cost, longest: sum and maximum over the modules of d_in + d_out.
-inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t slot_cost, int64_t longest, int64_t n_slots,
-                                    int64_t n_ex, int64_t T, bool ragged) {
+inline ProjFewPlan plan_project_few(bool bf16, int nk, bool tok, int64_t slot_cost, int64_t longest,
+                                    int64_t n_slots, int64_t n_ex, int64_t T, bool ragged) {
   ProjFewPlan P{};
   if (T > ((int64_t)1 << 24)) return P;  // (refused; the workspace query takes any length)
   if (bf16 || nk == 1) {
@@ -54,8 +65,8 @@ inline ProjFewPlan plan_project_few(bool bf16, int nk, int64_t slot_cost, int64_
     auto cost = [&](double c, double extra) {
       return valid + extra * (ragged && (double)T > c ? valid / c + 0.5 : std::ceil((double)T / c));
     };
-    const FewRule r = few_rule(bf16, nk);
-    const double behind = cost(64, 16) / r.rate - cost(project_chunk_tokens(nk, false), 64);
+    const FewRule r = few_rule(bf16, nk, tok);
+    const double behind = cost(64, 16) / r.rate - cost(project_chunk_tokens(nk, tok), 64);
     if (!((double)slot_cost * (double)n_ex * behind < r.lead * (double)longest)) return P;
   }
   // One token tile per workgroup where even then few workgroups exist and the

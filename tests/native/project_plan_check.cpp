@@ -22,7 +22,7 @@ int main() {
                 if ((double)mods * chunks * n > (double)(1 << 24)) continue;  // the call is refused
                 if (mods * n == 1 << 24) continue;  // one launch cannot take even one chunk: refused
                 const attr::ProjFewPlan P =
-                    attr::plan_project_few(bf16, nk, 2 * d * mods, 2 * d, mods, n, T, ragged);
+                    attr::plan_project_few(bf16, nk, false, 2 * d * mods, 2 * d, mods, n, T, ragged);
                 if (!P.ct) continue;
                 const size_t kk = (size_t)256 * nk * nk, part = mods * n * kk * 4;
                 bool ok = (P.ct == 16 || P.ct == 64) && (long long)P.n_chunks * P.ct >= T &&

@@ -3,7 +3,8 @@ plan depends on the widths' proportions, so layers shaped as a 1B model's, 32 ti
 narrower, take the kernels that the model's would.  ROUTES names the kernel that
 each case takes (checked on the CPU, in test_project_plan_cpu.py): groups of three,
 two and one in the general kernel, and both sides of the line between the kernels,
-shared input rows against separate copies.  References in fp64 on the GPU; bars as
+shared input rows against separate copies; TOKEN_ROUTES the same for per-token
+calls.  References in fp64 on the GPU; bars as
 in test_gpu_project_few.py: 1e-5 relative L2 per row for fp32, 1e-4 for bf16."""
 import pytest
 import torch
@@ -31,6 +32,14 @@ ROUTES = [("bf16", 16, 2, 16, 2048, False, "general"), ("bf16", 16, 2, 20, 2048,
           ("bf16", 32, 2, 4, 2048, False, "few 64"), ("bf16", 64, 2, 2, 1024, False, "few 64"),
           ("f32", 16, 2, 7, 2048, False, "few 64"), ("f32", 32, 2, 5, 700, True, "few 64"),
           ("f32", 64, 2, 3, 700, False, "few 64")]
+
+
+TOKEN_ROUTES = [("bf16", 16, 2, 16, 2048, False, "general"), ("bf16", 16, 2, 20, 2048, True, "general"),
+                ("bf16", 32, 2, 4, 2048, False, "general"), ("bf16", 32, 2, 7, 1500, True, "general"),
+                ("bf16", 64, 1, 5, 1030, False, "general"), ("bf16", 64, 1, 10, 700, True, "general"),
+                ("f32", 16, 2, 16, 2048, False, "general"), ("f32", 16, 2, 20, 2048, True, "general"),
+                ("bf16", 16, 2, 2, 2048, False, "few 64"), ("bf16", 32, 1, 3, 600, True, "few 64"),
+                ("bf16", 64, 1, 3, 300, True, "few 64"), ("f32", 32, 1, 4, 700, True, "few 64")]
 
 
 def make(dt, k, layers, n, T, ragged, shared=True):
@@ -82,3 +91,26 @@ def test_shared_rows_give_the_bits_of_separate_copies(dt, k, layers, n, T, ragge
         some = ref.norm(dim=1) > 0
         assert (got[~some] == 0).all() and (ln is None or (~some).sum() == (ln == 0).sum())
         assert ((got - ref).norm(dim=1)[some] <= bar * ref.norm(dim=1)[some]).all()
+
+
+@pytest.mark.parametrize("dt,k,layers,n,T,ragged,route", TOKEN_ROUTES)
+def test_token_blocks(dt, k, layers, n, T, ragged, route):
+    say(f"case: per token {dt} k={k} {layers} layers {n} x {T} lengths={ragged} ({route})")
+    mods, ln = make(dt, k, layers, n, T, ragged)
+    rows = n * T - 5  # the last rows are past the output
+    out = torch.full((rows + 5, len(mods) * k * k), 7.0, device="cuda")
+    P.attr_project_tokens(mods, k, n, T, out[:rows], length=ln)
+    pad = torch.zeros(n * T, dtype=torch.bool, device="cuda")
+    if ragged:
+        pad = torch.arange(T, device="cuda").repeat(n) >= ln.repeat_interleave(T)
+    written = ~pad
+    written[rows:] = False
+    assert (out[~written] == 7.0).all()
+    bar = 1e-5 if dt == "f32" else 1e-4
+    for m in mods:
+        x, y = (z.reshape(n * T, k)[written] for z in exact(m, n, T, ln))
+        got = out[written, m.out_col:m.out_col + k * k].reshape(-1, k, k)
+        for i in range(0, got.shape[0], 8192):
+            ref = x[i:i + 8192, :, None] * y[i:i + 8192, None, :]
+            err = (got[i:i + 8192].double() - ref).flatten(1).norm(dim=1)
+            assert (err <= bar * ref.flatten(1).norm(dim=1)).all()

@@ -28,16 +28,18 @@ def test_project_plan(tmp_path):
 
 
 def _routes(tmp_path, calls):
-    """[kernel] of calls (dtype, k, n_ex, T, lengths given, [(d_in, d_out)])."""
-    lines = "".join("%d %d %d %d %d %d %s\n" % (dt == "bf16", k, n, T, ragged, len(shapes),
-                                                " ".join("%d %d" % s for s in shapes))
-                    for dt, k, n, T, ragged, shapes in calls)
+    """[kernel] of calls (dtype, k, per-token, n_ex, T, lengths given, [(d_in, d_out)])."""
+    lines = "".join("%d %d %d %d %d %d %d %s\n" % (dt == "bf16", k, tok, n, T, ragged, len(shapes),
+                                                   " ".join("%d %d" % s for s in shapes))
+                    for dt, k, tok, n, T, ragged, shapes in calls)
     out = subprocess.run([_build("project_route", tmp_path)], input=lines, capture_output=True, text=True, check=True)
     return out.stdout.splitlines()
 
 
 def test_routes_of_the_gpu_cases(tmp_path):
     """The kernels that the GPU tests' cases are there for."""
-    from tests.test_gpu_project_routes import LAYER, ROUTES
-    calls = [(dt, k, n, T, ragged, [s[:2] for s in LAYER] * layers) for dt, k, layers, n, T, ragged, _ in ROUTES]
-    assert _routes(tmp_path, calls) == [r[-1] for r in ROUTES]
+    from tests.test_gpu_project_routes import LAYER, ROUTES, TOKEN_ROUTES
+    for cases, tok in ((ROUTES, False), (TOKEN_ROUTES, True)):
+        calls = [(dt, k, tok, n, T, ragged, [s[:2] for s in LAYER] * layers)
+                 for dt, k, layers, n, T, ragged, _ in cases]
+        assert _routes(tmp_path, calls) == [r[-1] for r in cases]
