@@ -896,10 +896,10 @@ hipError_t launch_project_main(bool bf16, int nk, const ProjTab* tab, const Proj
     if (nk == 1) { ATTR_MAIN_TK(true, 1) }
     else if (nk == 2) { ATTR_MAIN_TK(true, 2) }
     else { ATTR_MAIN_TK(true, 4) }
+  } else if (nk == 1) {
+    ATTR_MAIN_TK(false, 1)
   } else {
-    if (nk == 1) { ATTR_MAIN_TK(false, 1) }
-    else if (nk == 2) { ATTR_MAIN_TK(false, 2) }
-    else { ATTR_MAIN_TK(false, 4) }
+    return hipErrorInvalidConfiguration;  // fp32 at k = 32 and 64 takes the split kernel
   }
 #undef ATTR_MAIN_TK
 #undef ATTR_MAIN

@@ -23,6 +23,11 @@ int main() {
                 if (mods * n == 1 << 24) continue;  // one launch cannot take even one chunk: refused
                 const attr::ProjFewPlan P =
                     attr::plan_project_few(bf16, nk, false, 2 * d * mods, 2 * d, mods, n, T, ragged);
+                const bool always = !bf16 && nk > 1;  // fp32 at k = 32 and 64: no general kernel
+                if (always && (!P.ct || !attr::plan_project_few(bf16, nk, true, 2 * d * mods, 2 * d, mods, n, T, ragged).ct)) {
+                  std::printf("violation: fp32 nk=%d d=%lld mods=%lld n=%lld T=%lld: no split plan\n", nk, d, mods, n, T);
+                  return 1;
+                }
                 if (!P.ct) continue;
                 const size_t kk = (size_t)256 * nk * nk, part = mods * n * kk * 4;
                 bool ok = (P.ct == 16 || P.ct == 64) && (long long)P.n_chunks * P.ct >= T &&
