@@ -38,8 +38,11 @@ def _routes(tmp_path, calls):
 
 def test_routes_of_the_gpu_cases(tmp_path):
     """The kernels that the GPU tests' cases are there for."""
-    from tests.test_gpu_project_routes import LAYER, ROUTES, TOKEN_ROUTES
+    from tests.test_gpu_project_routes import LAYER, ROUTES, TOKEN_ROUTES, WIDE
     for cases, tok in ((ROUTES, False), (TOKEN_ROUTES, True)):
         calls = [(dt, k, tok, n, T, ragged, [s[:2] for s in LAYER] * layers)
                  for dt, k, layers, n, T, ragged, _ in cases]
         assert _routes(tmp_path, calls) == [r[-1] for r in cases]
+    wide = [(dt, k, tok, n, T, lengths is not None, shapes) for dt in ("bf16", "f32") for k in (16, 32, 64)
+            for tok in (False, True) for shapes, n, T, lengths in WIDE]
+    assert set(_routes(tmp_path, wide)) == {"few 16"}
