@@ -1224,6 +1224,9 @@ __global__ __launch_bounds__(SEL_NT) void score_merge_kernel(const float* __rest
   auto list_s = [&](int src) { return src < n_parts ? part_s + (q * n_parts + src) * (int64_t)k : top_s + q * (int64_t)k; };
   auto list_i = [&](int src) { return src < n_parts ? part_i + (q * n_parts + src) * (int64_t)k : top_i + q * (int64_t)k; };
   auto entry = [&](int src, int j) { return Cand{list_s(src)[j], list_i(src)[j]}; };
+  // A caller's previous list may hold -inf, or anything, under a valid index.
+  // -0 and +0 are equal scores: + 0.f makes both +0.
+  auto key_of = [](const Cand& c) -> uint32_t { return c.i < 0 ? 0u : c.s == c.s ? fkey(c.s + 0.f) : 1u; };
   const int room = n_src > 0 ? MERGE_E * SEL_NT / n_src : k;
   const int d = room < k ? room : k;
   Cand e4[MERGE_E];
@@ -1232,8 +1235,7 @@ __global__ __launch_bounds__(SEL_NT) void score_merge_kernel(const float* __rest
   for (int m = 0; m < MERGE_E; ++m) {
     const int e = t + SEL_NT * m, src = e / d;
     e4[m] = src < n_src ? entry(src, e - src * d) : cand_none();
-    // (a caller's previous list may hold -inf, or anything, under a valid index)
-    key[m] = e4[m].i < 0 ? 0u : e4[m].s == e4[m].s ? fkey(e4[m].s) : 1u;
+    key[m] = key_of(e4[m]);
   }
   uint32_t tau = block_kth<SEL_NT>(key, k, 16, kcnt);
   tau = tau ? tau : 1u;
@@ -1251,7 +1253,7 @@ __global__ __launch_bounds__(SEL_NT) void score_merge_kernel(const float* __rest
       if (e - src * d == d - 1)
         for (int j = d; j < k; ++j) {
           const Cand c = entry(src, j);
-          if (c.i < 0 || fkey(c.s) < tau) break;
+          if (key_of(c) < tau) break;
           take(c);
         }
     }
