@@ -21,6 +21,8 @@
 // Where rows are partitioned, the sorted lists are merged per query by a
 // threshold and a sort in (score desc, index asc) order, which also merges a
 // previous result when a store is scored chunk by chunk.
+#include <type_traits>
+
 #include "common.h"
 #include "gemm.h"
 #include "kernels.h"
@@ -661,27 +663,30 @@ __device__ inline uint64_t rs_key(uint32_t key, int64_t j) {
   return ((uint64_t)key << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
 }
 
-// A threshold at or below the k-th largest of the block's keys (V per thread, 0
-// = none) that at least k keys reach: exactly that key, or, with slack, the
-// first threshold found that at most k + slack keys reach.  0 when fewer than k
-// keys are there.  Two bits a step from the top, counted by ballots: 16 steps of
-// one barrier each, where a bitonic sort of 1024 keys takes 55 (k-th of the 256
-// prefix maxima of a query: 21 -> 5 us).  cnt: 48 counters in LDS.
-template <int NT, int V>
-__device__ inline uint32_t block_kth(const uint32_t (&key)[V], int k, int slack, int* cnt) {
+// A threshold at or below the k-th largest of the block's keys (key(v), v < V, per
+// thread; 0 = none; below 2^bits) that at least k keys reach: exactly that key, or,
+// with slack, the first threshold found that at most k + slack keys reach.  reach:
+// how many do.  0 (and reach 0) when fewer than k keys are there.  Two bits a step
+// from the top, counted by ballots: 16 steps of one barrier each for 32 bits, where
+// a bitonic sort of 1024 keys takes 55 (k-th of the 256 prefix maxima of a query:
+// 21 -> 5 us).  cnt: 48 counters in LDS.
+template <int V, typename F>
+__device__ inline uint32_t block_kth(F&& key, int k, int slack, int* cnt, int& reach, int bits = 32) {
   const int t = threadIdx.x;
   __syncthreads();  // the counters' last readers are done
   if (t < 48) cnt[t] = 0;
   __syncthreads();
   uint32_t T = 0u;
-  for (int it = 0; it < 16; ++it) {
-    const int sh = 30 - 2 * it;
+  reach = 0;
+  const int steps = (bits + 1) / 2;
+  for (int it = 0; it < steps; ++it) {
+    const int sh = 2 * (steps - 1 - it);
     int n[3] = {0, 0, 0};
 #pragma unroll
     for (int v = 0; v < V; ++v)
 #pragma unroll
       for (uint32_t b = 1; b <= 3; ++b)
-        n[b - 1] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[v] >= (T | (b << sh))));
+        n[b - 1] += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key(v) >= (T | (b << sh))));
     if ((t & 63) == 0) {
 #pragma unroll
       for (int b = 0; b < 3; ++b)
@@ -695,9 +700,20 @@ __device__ inline uint32_t block_kth(const uint32_t (&key)[V], int k, int slack,
         have = cnt[3 * it + b];
         T |= (uint32_t)(b + 1) << sh;
       }
+    reach = have ? have : reach;
     if (slack && have && have <= k + slack) break;  // uniform
   }
   return T;
+}
+
+// The block's sum of per-wave counts (n: uniform over the wave).
+__device__ inline int block_total(int n, int* cnt) {
+  __syncthreads();
+  if (threadIdx.x == 0) cnt[0] = 0;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0 && n) atomicAdd(cnt, n);
+  __syncthreads();
+  return cnt[0];
 }
 
 // Descending bitonic sort of n (a power of two) keys in LDS, 256 threads.
@@ -832,7 +848,8 @@ __global__ __launch_bounds__(256) void score_rselect_kernel(
       const uint32_t x = g < n_sc ? fkey(sm[g]) : 0u;
       key[u] = selectable(x) ? x : 0u;
     }
-    const uint32_t kth = block_kth<256>(key, k, 0, kcnt);
+    int reach;
+    const uint32_t kth = block_kth<RS_MAXSEG / 256>([&](int u) { return key[u]; }, k, 0, kcnt, reach);
     const uint32_t tau = kth ? kth : floor_key;
     c = collect(tau);
     ok = c <= RS_CAP;
@@ -1055,9 +1072,8 @@ __global__ __launch_bounds__(64) void score_small_select_kernel(
 }
 
 constexpr int SEL_NT = 1024;    // threads of the selection kernels below
-constexpr int SEL_CAP = 2048;   // entries gathered and sorted in LDS
 
-// Bitonic sort of n (a power of two, <= SEL_CAP) candidates, best first
+// Bitonic sort of n (a power of two) candidates, best first
 // ((score desc, index asc), empty entries last).
 __device__ inline void bitonic_cand(Cand* a, int n) {
   for (int size = 2; size <= n; size <<= 1)
@@ -1076,7 +1092,8 @@ __device__ inline void bitonic_cand(Cand* a, int n) {
   __syncthreads();
 }
 
-// Sorts the n <= SEL_CAP candidates of buf and writes the k best as a list.
+// Sorts the n candidates of buf (which holds the next power of two of them) and
+// writes the k best as a list.
 __device__ inline void write_best(Cand* buf, int n, int k, float* os, int64_t* oi) {
   int n2 = 1;
   while (n2 < n || n2 < k) n2 <<= 1;
@@ -1089,37 +1106,32 @@ __device__ inline void write_best(Cand* buf, int n, int k, float* os, int64_t* o
   }
 }
 
-// Best of the block's candidates (wb: SEL_NT / 64 entries in LDS).
-__device__ inline Cand block_best(Cand c, Cand* wb) {
-  c = wave_best(c);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) wb[threadIdx.x >> 6] = c;
-  __syncthreads();
-  Cand best = wb[0];
-#pragma unroll
-  for (int w = 1; w < SEL_NT / 64; ++w)
-    if (better(wb[w], best)) best = wb[w];
-  return best;
-}
-
 // Split-K plan with more than 256 rows (a store of fewer than 32768 rows):
 // one workgroup per query sums every row's slices (slice order) into registers,
 // rows u 1024 + t in thread t.  The k-th largest of the threads' best rows is
 // reached by k distinct rows, so the k best of all are at or above it; those
 // (random stores: k to 2 k rows), and the previous list when merging, are
-// gathered into LDS and sorted.  Should more than SEL_CAP qualify (massive ties)
-// the list is built by k rounds of block arg-max instead.  What bounds it is
-// latency: 1024 threads with VPT loads in flight each; 256 threads over parts of
-// 8192 rows with sorted segment maxima, and a merge of the parts, took 96 us for
-// 10 queries x 11335 rows, k = 100, and 30 us for 64 x 4096, k = 10.
+// gathered into LDS and sorted.  Where many more qualify (an all-zero query, many
+// copies of a row, the best rows in few threads), the k-th row of all is found by
+// score and, among equal scores, by index, and only the k best are gathered (8 x
+// 20000 x 2048, k = 100, all-zero queries: k rounds of arg-max over the registers
+// 690 us, now 50; sorted segment maxima, before, 178).  What bounds it is latency:
+// 1024 threads with VPT loads in flight each (at VPT = 32 ten registers spill); 256
+// threads over parts of 8192 rows with sorted segment maxima, and a merge of the
+// parts, took 96 us for 10 queries x 11335 rows, k = 100, and 30 us for 64 x 4096, k
+// = 10.
+constexpr int SEL_CAP = 1024;  // entries gathered and sorted in LDS: 3 k + 64 rows and a list
 template <int VPT>
 __global__ __launch_bounds__(SEL_NT) void score_split_select_kernel(
     const float* __restrict__ spart, int64_t nqp, int64_t n_g, int n_split, int k, int merge,
     int64_t index_base, float* top_s, int64_t* top_i) {
   __shared__ Cand buf[SEL_CAP];
-  __shared__ Cand wb[SEL_NT / 64];
   __shared__ int kcnt[48];
   __shared__ int cnt;
+  constexpr int NWAVE = SEL_NT / kWave;
+  __shared__ int tied_before[VPT][NWAVE];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (threadIdx.x == 0) cnt = 0;  // (block_kth's barriers follow)
   constexpr int SL = VPT == 32 ? 1 : VPT == 16 ? 2 : 8;  // slices loaded at once
   const int64_t q = blockIdx.x;
   const int t = threadIdx.x;
@@ -1131,12 +1143,20 @@ __global__ __launch_bounds__(SEL_NT) void score_split_select_kernel(
   for (int sp = 0; sp < n_split; sp += SL) {
     float x[SL][VPT];
 #pragma unroll
-    for (int a = 0; a < SL; ++a)
+    for (int a = 0; a < SL; ++a) {
+      const float* src = base + (sp + a) * plane;
+      // 32 rows a thread: through a descriptor of the slice, whose 32-bit offsets
+      // leave the registers to the scores (rows past the end read as zeros)
+      const __amdgpu_buffer_rsrc_t r = make_rsrc(src, (uint32_t)n_g * 4u);
 #pragma unroll
       for (int u = 0; u < VPT; ++u) {
-        const int64_t j = (int64_t)u * SEL_NT + t;
-        x[a][u] = j < n_g && sp + a < n_split ? base[(sp + a) * plane + j] : 0.f;
+        const int j = u * SEL_NT + t;
+        if (VPT == 32)
+          x[a][u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (uint32_t)j * 4u, 0, 0));
+        else
+          x[a][u] = j < (int)n_g && sp + a < n_split ? src[j] : 0.f;
       }
+    }
 #pragma unroll
     for (int a = 0; a < SL; ++a)
 #pragma unroll
@@ -1145,59 +1165,94 @@ __global__ __launch_bounds__(SEL_NT) void score_split_select_kernel(
   // NaN and -inf are never selected (key 0)
   auto key_of = [&](int u) -> uint32_t {
     const uint32_t key = fkey(v[u]);
-    return (int64_t)u * SEL_NT + t < n_g && selectable(key) ? key : 0u;
+    return u * SEL_NT + t < (int)n_g && selectable(key) ? key : 0u;
   };
-  uint32_t best_key[1] = {0u};
+  uint32_t best_key = 0u;
 #pragma unroll
   for (int u = 0; u < VPT; ++u) {
     const uint32_t key = key_of(u);
-    best_key[0] = key > best_key[0] ? key : best_key[0];
+    best_key = key > best_key ? key : best_key;
   }
-  uint32_t tau = block_kth<SEL_NT>(best_key, k, 16, kcnt);
+  int reach;
+  uint32_t tau = block_kth<1>([&](int) { return best_key; }, k, 16, kcnt, reach);
   tau = tau ? tau : 1u;
-  if (t == 0) cnt = 0;
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < VPT; ++u)
-    if (key_of(u) >= tau) {
-      const int pos = atomicAdd(&cnt, 1);
-      if (pos < SEL_CAP) buf[pos] = Cand{v[u], index_base + (int64_t)u * SEL_NT + t};
-    }
-  __syncthreads();
-  const int n = cnt;
-  float* os = top_s + q * k;
-  int64_t* oi = top_i + q * k;
-  if (n + (merge ? k : 0) <= SEL_CAP) {
-    if (merge)
-      for (int e = t; e < k; e += SEL_NT) {
-        const Cand c{os[e], oi[e]};
-        buf[n + e] = c.i >= 0 ? c : cand_none();
-      }
-    write_best(buf, n + (merge ? k : 0), k, os, oi);
-    return;
-  }
-  // fallback: round r takes the best candidate strictly after round r - 1's
-  Cand last = cand_none();
-  for (int r = 0; r < k; ++r) {
-    Cand tb = cand_none();
+  // Rows of at least tau, or (tied) those above it and, of those whose key is tau,
+  // the first `ties` in index order: tied_before[u][wave] counts the ties before
+  // this wave's rows u.
+  int ties = 0;
+  auto gather = [&](auto tied) {
+    int64_t row0 = index_base + t;
+    asm volatile("" : "+v"(row0));  // (the rows' indices are not held in registers meanwhile)
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
-      const Cand c = key_of(u) ? Cand{v[u], index_base + (int64_t)u * SEL_NT + t} : cand_none();
-      if (c.i >= 0 && (r == 0 || better(last, c)) && better(c, tb)) tb = c;
+      const uint32_t key = key_of(u);
+      bool pass = key >= tau;
+      if (decltype(tied)::value) {
+        const uint64_t at_tau = __builtin_amdgcn_ballot_w64(key == tau);
+        const int at = tied_before[u][wave] + __builtin_popcountll(at_tau & ((1ull << lane) - 1ull));
+        pass = key > tau || (key == tau && at < ties);
+      }
+      if (pass) {
+        const int pos = atomicAdd(&cnt, 1);
+        if (pos < SEL_CAP) buf[pos] = Cand{v[u], row0 + u * SEL_NT};
+      }
     }
-    if (merge && t < k) {
-      const Cand c{os[t], oi[t]};
-      if (c.i >= 0 && (r == 0 || better(last, c)) && better(c, tb)) tb = c;
+    __syncthreads();
+    return cnt;
+  };
+  auto rows_above = [&]() -> int {
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key_of(u) > tau));
+    return block_total(n, kcnt);
+  };
+  const int prev = merge ? k : 0;
+  // more rows than this cost more to gather and sort than to count out
+  const int most = 3 * k + 64;
+  int n = reach > k + 16 ? most + 1 : gather(std::false_type{});
+  if (n > most) {  // uniform
+    int above = rows_above();
+    if (above >= k) {  // the best rows sit in few threads: the k-th of all rows
+      tau = block_kth<VPT>(key_of, k, 0, kcnt, reach);
+      above = rows_above();
     }
-    last = block_best(tb, wb);
-    if (t == 0) buf[r] = last;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+      const int tied = __builtin_popcountll(__builtin_amdgcn_ballot_w64(key_of(u) == tau));
+      if (lane == 0) tied_before[u][wave] = tied;
+    }
+    __syncthreads();
+    if (wave == 0) {  // counts -> counts before, in row order (u, wave)
+      constexpr int E = VPT * NWAVE > kWave ? VPT * NWAVE / kWave : 1;  // per lane
+      int* c = &tied_before[0][0] + lane * E;
+      const bool mine = lane * E < VPT * NWAVE;
+      int sum = 0;
+      for (int e = 0; mine && e < E; ++e) sum += c[e];
+      int run = sum;
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int o = __shfl_up(run, off, kWave);
+        run += lane >= off ? o : 0;
+      }
+      run -= sum;
+      for (int e = 0; mine && e < E; ++e) {
+        const int x = c[e];
+        c[e] = run;
+        run += x;
+      }
+    }
+    ties = k - above;
+    if (t == 0) cnt = 0;
+    __syncthreads();
+    n = gather(std::true_type{});  // k
   }
-  __syncthreads();
-  for (int j = t; j < k; j += SEL_NT) {
-    const Cand c = buf[j];
-    os[j] = c.i >= 0 ? c.s : -__builtin_inff();
-    oi[j] = c.i >= 0 ? c.i : -1;
+  float* os = top_s + q * k;
+  int64_t* oi = top_i + q * k;
+  for (int e = t; e < prev; e += SEL_NT) {
+    const Cand c{os[e], oi[e]};
+    buf[n + e] = c.i >= 0 ? c : cand_none();
   }
+  write_best(buf, n + prev, k, os, oi);
 }
 
 // One workgroup per query merges n_parts + merge <= 1024 sorted lists.  The
@@ -1205,17 +1260,20 @@ __global__ __launch_bounds__(SEL_NT) void score_split_select_kernel(
 // all) are loaded side by side; the k-th best of them is a lower bound on the
 // k-th best overall, and the entries at or above it (a prefix of each list; past
 // d entries the list's last thread goes on alone) are gathered into LDS and
-// sorted.  Past SEL_CAP such entries (massive ties) the merge is k rounds of
-// block arg-max over the list heads instead.  Latency-bound: one thread per list
-// walking its prefix, between two sorts of 256 threads, took 30-41 us at k = 100
-// over 512 lists as over two.
-constexpr int MERGE_E = 4;  // entries per thread of the first load
+// sorted.  Where more than a few entries share the k-th score (an all-zero query:
+// every score is 0) the bound is by index too, so that at most k + slack of the
+// loaded entries pass, at most (k + slack) / d lists go on, and all of them fit.
+// rows: the lists' indices are index_base .. index_base + rows - 1.
+// Latency-bound: one thread per list walking its prefix, between two sorts of 256
+// threads, took 30-41 us at k = 100 over 512 lists as over two.
+constexpr int MERGE_E = 4;       // entries per thread of the first load
+constexpr int MERGE_CAP = 4096;  // k + (k / d) (k - d) <= 4096 for k <= 128, d >= 4
 __global__ __launch_bounds__(SEL_NT) void score_merge_kernel(const float* __restrict__ part_s,
                                                              const int64_t* __restrict__ part_i,
                                                              int n_parts, int k, int merge,
+                                                             int64_t index_base, uint32_t rows,
                                                              float* top_s, int64_t* top_i) {
-  __shared__ Cand buf[SEL_CAP];
-  __shared__ Cand wb[SEL_NT / 64];
+  __shared__ Cand buf[MERGE_CAP];
   __shared__ int kcnt[48];
   __shared__ int cnt;
   const int64_t q = blockIdx.x;
@@ -1237,51 +1295,51 @@ __global__ __launch_bounds__(SEL_NT) void score_merge_kernel(const float* __rest
     e4[m] = src < n_src ? entry(src, e - src * d) : cand_none();
     key[m] = key_of(e4[m]);
   }
-  uint32_t tau = block_kth<SEL_NT>(key, k, 16, kcnt);
+  const int slack = k + 16 + (k + 16) / d * (k - d) <= MERGE_CAP ? 16 : 0;
+  int reach;
+  uint32_t tau = block_kth<MERGE_E>([&](int m) { return key[m]; }, k, slack, kcnt, reach);
+  // Index order as 32-bit keys, larger is earlier: this call's rows, and before and
+  // after them the previous list's other entries (j: their place in it).
+  auto before = [&](const Cand& c, int j) -> uint32_t {
+    const int64_t r = c.i - index_base;
+    return rows + 256u - (r < 0 ? (uint32_t)j : r < (int64_t)rows ? 128u + (uint32_t)r : 128u + rows + (uint32_t)j);
+  };
+  uint32_t tie = 0u;  // of the entries whose key is tau, those with before() >= tie
+  if (reach > k + slack) {
+    int above = 0;
+#pragma unroll
+    for (int m = 0; m < MERGE_E; ++m) above += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[m] > tau));
+    above = block_total(above, kcnt);
+    tie = block_kth<MERGE_E>([&](int m) { return key[m] == tau ? before(e4[m], (t + SEL_NT * m) % d) : 0u; },
+                             k - above, 0, kcnt, reach, 32 - __builtin_clz(rows + 256u));
+  }
   tau = tau ? tau : 1u;
   if (t == 0) cnt = 0;
   __syncthreads();
+  auto passes = [&](const Cand& c, int j) {
+    const uint32_t ck = key_of(c);
+    return ck > tau || (ck == tau && before(c, j) >= tie);
+  };
   auto take = [&](const Cand& c) {
     const int pos = atomicAdd(&cnt, 1);
-    if (pos < SEL_CAP) buf[pos] = c;
+    if (pos < MERGE_CAP) buf[pos] = c;
   };
 #pragma unroll
   for (int m = 0; m < MERGE_E; ++m)
-    if (key[m] >= tau) {
+    if (key[m] >= tau && passes(e4[m], (t + SEL_NT * m) % d)) {
       take(e4[m]);
       const int e = t + SEL_NT * m, src = e / d;
       if (e - src * d == d - 1)
         for (int j = d; j < k; ++j) {
           const Cand c = entry(src, j);
-          if (key_of(c) < tau) break;
+          if (!passes(c, j)) break;
           take(c);
         }
     }
   __syncthreads();
-  const int n = cnt;
-  float* os = top_s + q * (int64_t)k;
-  int64_t* oi = top_i + q * (int64_t)k;
-  if (n <= SEL_CAP) {
-    write_best(buf, n, k, os, oi);
-    return;
-  }
-  int head = 0;
-  Cand cur = t < n_src ? entry(t, 0) : cand_none();
-  for (int j = 0; j < k; ++j) {
-    const Cand best = block_best(cur, wb);
-    if (t == 0) buf[j] = best;
-    // the list whose head won advances (indices are unique across lists)
-    if (best.i >= 0 && cur.i == best.i && cur.s == best.s) {
-      ++head;
-      cur = head < k ? entry(t, head) : cand_none();
-    }
-  }
-  __syncthreads();
-  for (int j = t; j < k; j += SEL_NT) {
-    const Cand c = buf[j];
-    os[j] = c.i >= 0 ? c.s : -__builtin_inff();
-    oi[j] = c.i >= 0 ? c.i : -1;
-  }
+  // (more than the buffer holds only from a previous list that names an index
+  // many times)
+  write_best(buf, cnt < MERGE_CAP ? cnt : MERGE_CAP, k, top_s + q * (int64_t)k, top_i + q * (int64_t)k);
 }
 
 }  // namespace
@@ -1418,7 +1476,8 @@ __global__ __launch_bounds__(256) void score_bound_kernel(const float* __restric
     const uint32_t x = i < nb ? fkey(seg_s[q * nb + i]) : 0u;
     key[u] = selectable(x) ? x : 0u;
   }
-  const uint32_t kth = block_kth<256>(key, k, 0, kcnt);
+  int reach;
+  const uint32_t kth = block_kth<4>([&](int u) { return key[u]; }, k, 0, kcnt, reach);
   if (threadIdx.x == 0) bound[q] = kth ? fkey_inv(kth) : -__builtin_inff();
 }
 
@@ -1559,7 +1618,8 @@ hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int
     return hipGetLastError();
   }
   hipLaunchKernelGGL(score_merge_kernel, dim3((unsigned)n_q), dim3(SEL_NT), 0, s,
-                     (const float*)part_s, (const int64_t*)part_i, n_parts, k, merge, top_s, top_i);
+                     (const float*)part_s, (const int64_t*)part_i, n_parts, k, merge, index_base, (uint32_t)n_g, top_s,
+                     top_i);
   return hipGetLastError();
 }
 

@@ -35,3 +35,34 @@ def test_zeros_of_either_sign_are_equal(nq, n, D, dt, k):
     ts, ti = _topk(Q, G, k, prev=([-0.0, -0.0][:k], [3, 7][:k]))
     want = ([3, 7] + list(range(1000, 1000 + k)))[:k]
     assert (ti == torch.tensor(want, device="cuda")).all() and (ts == 0).all()
+
+
+@pytest.mark.parametrize("nq,n,D", PLANS + [(1, 32000, 1024), (1, 600, 64), (3, 300000, 256)])
+@pytest.mark.parametrize("dt", [torch.float16, torch.float32])
+@pytest.mark.parametrize("k", [1, 10, 100, 128])
+@pytest.mark.parametrize("merge", [False, True])
+def test_mass_ties(nq, n, D, dt, k, merge):
+    """An all-zero query (every score 0), one whose scores take three values, and an
+    ordinary one, on integers (exact scores): the list is the stable sort's."""
+    if n > 200000 and dt == torch.float32 and k != 100:
+        pytest.skip("one k of the large fp32 store")
+    say(f"case: ties nq={nq} n={n} D={D} {dt} k={k} merge={merge}")
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    G = torch.randint(-2, 3, (n, D), generator=g, device="cuda").to(dt)
+    G[:, 0] = torch.randint(0, 3, (n,), generator=g, device="cuda").to(dt)
+    Q = torch.zeros((nq, D), dtype=dt, device="cuda")
+    if nq > 1:
+        Q[1, 0] = 1
+    if nq > 2:
+        Q[2:] = torch.randint(-2, 3, (nq - 2, D), generator=g, device="cuda").to(dt)
+    prev = ([2.0, 2.0, 0.0, -1.0][:k], [4, 900, 17, 2][:k]) if merge else None
+    ts, ti = _topk(Q, G, k, prev)
+    S = Q.float() @ G.float().T
+    idx = torch.arange(1000, 1000 + n, device="cuda").expand(nq, n)
+    if merge:
+        s, i = (torch.tensor(x, device="cuda").expand(nq, len(x)) for x in prev)
+        S, idx = torch.cat([s.float(), S], 1), torch.cat([i, idx], 1)
+        order = torch.argsort(idx, dim=1, stable=True)
+        S, idx = S.gather(1, order), idx.gather(1, order)
+    order = torch.sort(S, dim=1, descending=True, stable=True).indices[:, :k]
+    assert torch.equal(ts, S.gather(1, order)) and torch.equal(ti, idx.gather(1, order))
