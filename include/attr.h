@@ -215,7 +215,12 @@ attr_status attr_precond_accumulate(const void* X, attr_dtype x_dtype, int64_t n
  * A_hi = fp16(A), A_lo = fp16(A - A_hi), y = 2^-s X (A_hi + A_lo)^T on fp16
  * MFMA with fp32 accumulation (about 22 significant bits of M).  Few rows (a
  * session's queries: up to 2^23 / D, and at most D) take a path that reads M
- * once and scales each of its rows on its own.
+ * once and scales each of its rows on its own; its sums have another order, so
+ * the last bits of a row depend on n_rows.
+ * With unit_normalize a row that holds a NaN after the first step keeps it and
+ * is zero elsewhere; so does one that holds an infinity (as NaN).  Squares are
+ * summed in fp32, and a row whose sum passes fp32's range is written as zeros;
+ * FULL on few rows sums them in fp64.
  *
  *   X, ldx   device [n_rows, D], x_dtype ATTR_F32 or ATTR_F16
  *            (FULL: ATTR_F16 only)

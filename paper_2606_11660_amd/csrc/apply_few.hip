@@ -345,8 +345,9 @@ __global__ __launch_bounds__(256) void apply_few_final_kernel(const float* __res
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
     ss = (red[0] + red[1]) + (red[2] + red[3]);
-    // a zero row stays zero; a row with a NaN is written as NaN
-    sc = ss == 0.0 ? 0.f : (float)(1.0 / sqrt(ss));
+    // a zero row stays zero; a row with a NaN keeps it and is zero elsewhere, as
+    // on the general path
+    sc = ss > 0.0 ? (float)(1.0 / sqrt(ss)) : 0.f;
   }
   YT* y = Y + r * ldy;
 #pragma unroll

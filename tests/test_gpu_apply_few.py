@@ -80,3 +80,19 @@ def test_apply_few_nan_stays_in_its_column():
     P.attr_precond_apply(X, P.PRECOND_FULL, M, False, Y)
     bad = torch.isnan(Y)
     assert bad[:, 77].all() and bad.sum().item() == 40
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_rows_with_nan_are_those_of_the_general_path(dtype):
+    """unit rows: a NaN stays where it is and the row is zero elsewhere, in a call of
+    few rows as in one of more than D rows (the general path)."""
+    X, M = _case(520, 512, 4)
+    X[3] = float("nan")
+    M[77, 100] = float("nan")
+    few, many = (torch.full((n, 512), 7.0, dtype=dtype, device="cuda") for n in (40, 520))
+    P.attr_precond_apply(X[:40], P.PRECOND_FULL, M, True, few)
+    P.attr_precond_apply(X, P.PRECOND_FULL, M, True, many)
+    for Y in (few, many):
+        bad = torch.isnan(Y)
+        assert bad[3].all() and bad[:, 77].all() and bad.sum() == 512 + Y.shape[0] - 1
+        assert (Y[~bad] == 0).all()
