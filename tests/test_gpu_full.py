@@ -199,3 +199,33 @@ def test_full_apply_unit_rows_beyond_fp16_range():
         err = row_rel_l2(got, ref)
         say(f"y={ydt} max row rel-L2 {err.max():.2e}")
         assert err.max() <= 2e-3
+
+
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+def test_full_apply_beyond_fp16_range_in_a_call_of_many_rows(ydt):
+    """The rows of the test above in a call of more rows than D, which takes the
+    general path: with an fp16 Y its intermediate is fp16, scaled per 128-column
+    segment by an exponent that the second pass takes back."""
+    say("case: full apply, rows beyond fp16 range among many")
+    D, N = 512, 20000
+    F = synth.lowrank_factor(D, 64, seed=3)
+    X = synth.lowrank_rows(0, N, D=D, rank=64, chunk=8192, F=F)
+    M, lam = O.finalize_full(O.accumulate_full(X), N)
+    _, V = np.linalg.eigh(O.accumulate_full(X) / N)
+    v = V[:, 0] / np.abs(V[:, 0]).max()
+    rng = np.random.default_rng(5)
+    far = np.stack([30000.0 * v, 30000.0 * v + 100.0 * rng.standard_normal(D), -20000.0 * v,
+                    5e-7 * rng.standard_normal(D)]).astype(np.float16)
+    Q = np.concatenate([far, X[:D].astype(np.float16), far])
+    M32 = M.astype(np.float32)
+    ref = O.precond_apply(Q, "full", M32.astype(np.float64), unit_norm=True)
+    raw = O.precond_apply(far, "full", M32.astype(np.float64), unit_norm=False)
+    assert np.abs(raw[:3]).max(axis=1).min() > 65504 and np.abs(raw[3]).max() < 6.1e-5
+    Y = torch.empty((Q.shape[0], D), dtype=ydt, device="cuda")
+    P.attr_precond_apply(dev(Q), P.PRECOND_FULL, dev(M32), True, Y)
+    torch.cuda.synchronize()
+    got = host(Y).astype(np.float64)
+    assert np.isfinite(got).all()
+    err = row_rel_l2(got, ref)
+    say(f"y={ydt} max row rel-L2 {err.max():.2e}")
+    assert err.max() <= 2e-3
