@@ -205,26 +205,29 @@ class Workspace:
     before the work queued on those streams has finished.
     """
 
-    # the buffer whose streams of use have been recorded, and those streams
-    _recorded_on: Optional[torch.Tensor] = None
-    _recorded: set = set()
-
     def __init__(self, device=None):
         self.device = torch.device(device or "cuda")
-        self.buf: Optional[torch.Tensor] = None
+        self.buf = None
+
+    @property
+    def buf(self) -> Optional[torch.Tensor]:
+        return self._buf
+
+    @buf.setter
+    def buf(self, buf: Optional[torch.Tensor]) -> None:
+        self._buf = buf
+        self._streams = set()  # the raw streams recorded on it
 
     def get(self, nbytes: int, stream=None) -> Tuple[Optional[int], int]:
         if nbytes == 0:
             return None, 0
-        if self.buf is None or self.buf.numel() < nbytes:
+        if self._buf is None or self._buf.numel() < nbytes:
             self.buf = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
-        if self._recorded_on is not self.buf:
-            self._recorded_on, self._recorded = self.buf, set()
         raw = _stream(stream)
-        if raw not in self._recorded:
-            self.buf.record_stream(_torch_stream(stream))
-            self._recorded.add(raw)
-        return self.buf.data_ptr(), self.buf.numel()
+        if raw not in self._streams:
+            self._buf.record_stream(_torch_stream(stream))
+            self._streams.add(raw)
+        return self._buf.data_ptr(), self._buf.numel()
 
 
 _default_ws: Dict[Tuple[torch.device, int], Workspace] = {}
