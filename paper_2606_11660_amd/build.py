@@ -234,6 +234,23 @@ def _marshal_command(out: str) -> list:
             "-o", out]
 
 
+def build_marshal() -> bool:
+    """Build the binding's native part.  It is optional (the binding has the same
+    checks in Python) and needs what the library does not: g++ and the headers of this
+    torch, one of them private.  Where it cannot be built, say so and leave none."""
+    tmp = MARSHAL + ".tmp"
+    try:
+        _run(_marshal_command(tmp))
+        os.replace(tmp, MARSHAL)
+        return True
+    except (RuntimeError, ImportError, OSError, AttributeError) as e:
+        for stale in (tmp, MARSHAL):
+            if os.path.exists(stale):
+                os.remove(stale)
+        print(f"_marshal.so was not built, projection calls check their modules in Python: {e}", file=sys.stderr)
+        return False
+
+
 def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
     os.makedirs(BUILD, exist_ok=True)
@@ -249,8 +266,6 @@ def build(verbose: bool = False) -> str:
         jobs.append([hipcc, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__",
                      f"-I{ROCM}/include", "-c", os.path.join(CSRC, src), "-o", obj])
     objs = [j[-1] for j in jobs]
-    marshal_tmp = MARSHAL + ".tmp"
-    marshal_job = _marshal_command(marshal_tmp)
     # device assembly of every HIP source, checked for unprotected loads
     asm_jobs = []
     for src in HIP_SOURCES:
@@ -259,9 +274,11 @@ def build(verbose: bool = False) -> str:
             asm_jobs.append([hipcc, *COMMON, *DEVICE, "--cuda-device-only", "-S", "-x", "hip", path,
                              "-o", os.path.join(BUILD, src + ".s")])
     with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs) + len(asm_jobs))) as ex:
-        for out in ex.map(_run, [marshal_job] + jobs + asm_jobs):
+        marshal = ex.submit(build_marshal)
+        for out in ex.map(_run, jobs + asm_jobs):
             if verbose and out.strip():
                 print(out)
+        marshal.result()
     hazards = []
     for j in asm_jobs:
         with open(j[-1]) as f:
@@ -272,7 +289,6 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     _run([hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
-    os.replace(marshal_tmp, MARSHAL)
     return LIB
 
 
