@@ -798,7 +798,7 @@ def main():
                    "global_batch": B, "seq_len": T, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS, "traffic": _measured_traffic(),
-                     "kernel": "attr_project call: project_pack_kernel (x5) + project_main_kernel"
+                     "kernel": "attr_project call: project_pack_kernel (x3) + project_main_kernel"
                                "<bf16,k=16> + project_reduce_kernel",
                      "bytes_per_launch": proj_bytes, "ms_per_launch": proj_ms,
                      "tokens_per_launch": float(np.mean([tokens[i % len(batches)]

@@ -20,7 +20,9 @@
 //    the exponent (2 bits of headroom below); the waves then scale their sums
 //    of that row by the same power of two (exact).  hi + lo keeps 22 bits of
 //    every value within 2^-12 of its row's running maximum, and an absolute
-//    2^-37 of that maximum below, as the general path does against max|M|.
+//    2^-37 of that maximum below.  (The general path's floor is 2^-39 of max|M|:
+//    lower in the rows that hold max|M|, higher where a row's own maximum is less
+//    than a quarter of it.)
 //  * One barrier per two stages (four LDS stage buffers).
 // The sums go to fp32 partials per K-slice, [slice][row][D]; a second kernel
 // adds the slices in order, forms the row's norm and writes Y with a single

@@ -18,9 +18,10 @@
 //    (tile, D-slice) pairs and write fp32 partial scores; one workgroup per
 //    query sums the slices in slice order and selects by a threshold from
 //    its threads' best rows and a sort.
-// Where rows are partitioned, the sorted lists are merged per query by a
-// threshold and a sort in (score desc, index asc) order, which also merges a
-// previous result when a store is scored chunk by chunk.
+// Where rows are partitioned, the sorted lists are merged per query in (score
+// desc, index asc) order by a threshold and a sort (k up to 8: by rounds of
+// arg-max), which also merges a previous result when a store is scored chunk by
+// chunk.
 #include <type_traits>
 
 #include "common.h"
