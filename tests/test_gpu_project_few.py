@@ -1,9 +1,12 @@
 """The projection's two kernels (contraction split over the waves; one chunk
 per wave) at the edges of their token tiles and chunks: lengths around 16, 64
 and 256 tokens, empty examples, NaN padding, widths of one K-group, one chunk
-per example (written straight to the output) and many.  The multi-chunk calls
-run twice: with the queried workspace and with the least that the call accepts,
-which holds the partials of the general kernel only.  Bars: 1e-5 relative L2
+per example (written straight to the output) and many.  At these sizes the
+pooled calls take the split kernel and the per-token calls whichever their own
+rule names; the pooled general kernel on ragged rows is compared with the split
+one in test_gpu_project_routes.py.  The multi-chunk calls run twice: with the
+queried workspace and with the least that the call accepts, which holds the
+partials of fewer chunks, so that they run in several rounds.  Bars: 1e-5 relative L2
 per row for fp32 (sums of at most 2048 fp32 terms and products: 2^-24 sqrt(2048)
 = 2.7e-6), 1e-4 for bf16 (inputs exact, the same sums); a token's block has the
 same bars."""
