@@ -29,8 +29,9 @@
 // rounding (no fp16 intermediate).  Deterministic.
 // 256 rows x 8192: 628 us on the general path (max|M| 152, split 149, GEMM
 // 316, norm 7) -> 93-103 us (this kernel 79 us, 3.4 TB/s of M, packing X 5,
-// final 6.5); up to 64 rows the kernel reads M at 5.7 TB/s.  At 256 rows it
-// waits for X's fragments: X passes through the L2 once per 64 columns of Y.
+// final 6.5); up to 64 rows the kernel reads M at 5.7 TB/s.  At 256 rows the
+// fragments of X pass through the L2 once per 64 columns of Y (537 MB), and the
+// third of them that misses it comes beside M's 268 MB: 443 MB, 5.65 TB/s.
 // Tried: more stages in flight (6, 8), one barrier per stage, two workgroups
 // per CU at 64 rows, MFMAs and split interleaved by hand: no change.
 #include "common.h"
