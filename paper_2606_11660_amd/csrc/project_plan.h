@@ -70,12 +70,24 @@ inline ProjFewPlan plan_project_few(bool bf16, int nk, bool tok, int64_t slot_co
     if (!((double)slot_cost * (double)n_ex * behind < r.lead * (double)longest)) return P;
   }
   // One token tile per workgroup where even then few workgroups exist and the
-  // modules are wide: R and S are read four times as often (one 149-token
-  // example of 2 1B-shaped layers: 40 -> 29 us; of 128 tokens over 12
-  // GPT-2-shaped layers: 28 -> 32 us).
+  // modules are wide: the longest module's chain is shorter, R and S are read four
+  // times as often (one 149-token example of 2 1B-shaped layers: 40 -> 29 us; of 128
+  // tokens over 12 GPT-2-shaped layers: 28 -> 32 us).  A summed call pays for the
+  // partials of more chunks, k x k each, and in bf16 for a reduce where 64 tokens
+  // hold an example, while the chain of the matrix products grows with k only in
+  // fp32: so from k = 32 in bf16 and at k = 64 in fp32 the longest module has to be
+  // worth them.  16 / 64 tokens, bf16, k = 64: one GPT-2-shaped layer of 300 tokens 90
+  // / 50 us (the general kernel 72), of 512 134 / 62 (83), 2 1B-shaped layers of 300
+  // tokens 132 / 90, of 16 tokens 42 / 49, a module of 8192 x 28672 and 128 tokens
+  // 156 / 202; k = 32: one GPT-2-shaped layer of 512 tokens 46 / 32, 2 1B-shaped layers of
+  // 149 44 / 54; fp32, k = 64: one GPT-2-shaped layer of 149 tokens 73 / 90, of 512
+  // 153 / 110.
   // (in double: the workspace query takes any count)
   const double blocks = (double)n_slots * (double)((T + 15) / 16) * (double)n_ex;
-  P.ct = blocks * 24 <= (double)(slot_cost / n_slots) ? 16 : 64;
+  const double more = (double)((T + 15) / 16 - (T + 63) / 64) + (bf16 && T <= 64 ? 6 : 0);
+  const double worth = bf16 ? (nk == 1 ? 0 : nk == 2 ? 580 : 1800) : (nk == 4 ? 320 : 0);
+  const bool one = tok || T <= 16 || (double)longest >= worth * more;
+  P.ct = one && blocks * 24 <= (double)(slot_cost / n_slots) ? 16 : 64;
   P.n_chunks = (int)((T + P.ct - 1) / P.ct);
   return P;
 }

@@ -42,9 +42,9 @@ TOKEN_ROUTES = [("bf16", 16, 2, 16, 2048, False, "general"), ("bf16", 16, 2, 20,
                 ("bf16", 64, 1, 3, 300, True, "few 64"), ("f32", 32, 1, 4, 700, True, "few 64")]
 
 # shapes, examples, T, lengths
-WIDE = [([(2048, 2048)], 1, 1, None), ([(2048, 2048)], 1, 16, None), ([(2048, 2048)], 1, 17, None),
-        ([(1024, 4096), (2048, 2048)], 1, 149, None), ([(2048, 2048)], 1, 16, [15]), ([(2048, 2048)], 2, 1, [0, 1]),
-        ([(1024, 4096), (2048, 2048)], 3, 40, [33, 0, 16]), ([(4096, 1024)], 2, 149, [149, 130])]
+WIDE = [([(2048, 2048)], 1, 1, None), ([(2048, 2048)], 1, 16, None), ([(4096, 8704)], 1, 17, None),
+        ([(4096, 8704), (4096, 4096)], 1, 149, None), ([(2048, 2048)], 1, 16, [15]), ([(2048, 2048)], 2, 1, [0, 1]),
+        ([(8192, 6400), (2048, 6400)], 3, 40, [33, 0, 16]), ([(8192, 4608)], 2, 149, [149, 130])]
 
 
 def make(dt, k, layers, n, T, ragged, shared=True, layer=LAYER, lengths=None):

@@ -46,3 +46,19 @@ def test_routes_of_the_gpu_cases(tmp_path):
     wide = [(dt, k, tok, n, T, lengths is not None, shapes) for dt in ("bf16", "f32") for k in (16, 32, 64)
             for tok in (False, True) for shapes, n, T, lengths in WIDE]
     assert set(_routes(tmp_path, wide)) == {"few 16"}
+
+
+GPT2, LLAMA_1B = [(768, 2304), (768, 768), (768, 3072), (3072, 768)], [(2048, 2048)] * 4 + [(2048, 8192)] * 2 + [(8192, 2048)]
+
+
+@pytest.mark.parametrize("dt,k,shapes,T,summed", [
+    ("bf16", 16, GPT2, 512, "few 16"), ("bf16", 32, GPT2, 512, "few 64"), ("bf16", 32, LLAMA_1B * 2, 149, "few 16"),
+    ("bf16", 64, GPT2, 16, "few 16"), ("bf16", 64, GPT2, 17, "few 64"), ("bf16", 64, GPT2, 300, "few 64"),
+    ("bf16", 64, GPT2 * 2, 256, "few 64"), ("bf16", 64, LLAMA_1B * 2, 300, "few 64"),
+    ("bf16", 64, [(8192, 28672)], 149, "few 16"), ("f32", 32, GPT2, 512, "few 16"),
+    ("f32", 64, GPT2, 149, "few 16"), ("f32", 64, GPT2, 512, "few 64")])
+def test_token_tiles_of_few_items(tmp_path, dt, k, shapes, T, summed):
+    """Summed calls take 16 tokens per workgroup only where the modules are wide enough
+    for the partials of more chunks; per-token calls have no partials."""
+    calls = [(dt, k, tok, 1, T, False, shapes) for tok in (False, True)]
+    assert _routes(tmp_path, calls) == [summed, "few 16"]
