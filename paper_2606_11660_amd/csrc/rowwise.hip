@@ -358,17 +358,40 @@ hipError_t launch_rowscale_t(const void* X, int64_t ldx, int64_t n_rows, int64_t
                        dim3(T), 0, s, x, ldx, n_rows, D, m, unit, y, ldy);                         \
     return hipGetLastError();                                                                      \
   }
+  // Which calls take rowscale_rows_kernel (general / this kernel, us; one and two rows
+  // per workgroup give the same bits, so a row's do not depend on the other rows).
+  constexpr bool XF = sizeof(TX) == 4, YF = sizeof(TY) == 4;
   if (!row_ss && n8 <= 4096) {
-    if (m && n8 > 1024) {  // (up to 1024: the two-row kernel below)
-      if (n8 <= 1536) ATTR_RR(512, 3, 2, true)
-      if (n8 <= 2048) ATTR_RR(512, 4, 2, true)
-      if (n8 <= 3072) ATTR_RR(1024, 3, 2, true)
-      ATTR_RR(1024, 4, 2, true)
+    // With a scale: fp32 rows to fp32 do not gain (60000 x 16384 1531 / 1668).  One row
+    // per workgroup while there are few (general / one / two): 64 x 24096 fp16 9.7 / 5.8 /
+    // 8.2, fp32 to fp16 7.7 / 6.6 / 11.9; 1000 x 12288 fp16 11.4 / 12.9 / 11.1; 20000 x
+    // 12288 fp32 to fp16 291 / 274 / 267.  fp32 to fp16 stays up to 11% behind for 300
+    // to 700 rows (part of a second wave of workgroups: 512 x 12288 8.1 / 8.7 / 10.6).
+    if constexpr (!(XF && YF)) {
+      if (m && n8 > 1024) {  // (up to 1024: the two-row kernel below)
+        const bool narrow = n8 <= 2048;
+        const int64_t one = XF ? (narrow ? 8192 : 1024) : YF ? (narrow ? 10000 : n_rows + 1) : narrow ? 512 : 256;
+        if (n_rows <= one) {
+          if (n8 <= 1536) ATTR_RR(512, 3, 1, true)
+          if (n8 <= 2048) ATTR_RR(512, 4, 1, true)
+          if (n8 <= 3072) ATTR_RR(1024, 3, 1, true)
+          ATTR_RR(1024, 4, 1, true)
+        }
+        if (n8 <= 1536) ATTR_RR(512, 3, 2, true)
+        if (n8 <= 2048) ATTR_RR(512, 4, 2, true)
+        if constexpr (XF == YF || XF) {
+          if (n8 <= 3072) ATTR_RR(1024, 3, 2, true)
+          ATTR_RR(1024, 4, 2, true)
+        }
+      }
     }
-    // without a scale one row per 256 threads is as fast up to 16384 columns
-    if (!m && n8 > 2048) {
-      if (n8 <= 3072) ATTR_RR(1024, 3, 1, false)
-      ATTR_RR(1024, 4, 1, false)
+    // Without a scale one row per 256 threads is as fast up to 16384 columns, and
+    // faster for large stores of fp16 rows to fp32 (20000 x 32768 822 / 1157).
+    if constexpr (XF || !YF) {
+      if (!m && n8 > 2048) {
+        if (n8 <= 3072) ATTR_RR(1024, 3, 1, false)
+        ATTR_RR(1024, 4, 1, false)
+      }
     }
   }
 #undef ATTR_RR

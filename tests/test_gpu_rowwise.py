@@ -1,4 +1,4 @@
-"""The wide-row normaliser (more than 8192 columns: two rows per workgroup, 512
+"""The wide-row normaliser (more than 8192 columns: one or two rows per workgroup, 512
 or 1024 threads, three or four chunks each) and the column sums at the edges of
 their layouts: widths one chunk past and at each limit, odd row counts, in place,
 with and without scale and norm.  Bars: one fp16 ulp (2^-11 relative, plus half a
@@ -40,6 +40,29 @@ def test_wide_rows(D, dtype, n):
             Y = torch.empty_like(Z)
             P.attr_precond_apply(X, mode, scale, unit, Y)
             assert torch.equal(Z, Y)
+
+
+@pytest.mark.parametrize("xd,yd,D,n", [
+    (torch.float16, torch.float16, 8200, 513), (torch.float16, torch.float16, 16384, 512),
+    (torch.float16, torch.float16, 24576, 257), (torch.float16, torch.float32, 12288, 10001),
+    (torch.float16, torch.float32, 24584, 300), (torch.float32, torch.float16, 16384, 8193),
+    (torch.float32, torch.float16, 24576, 1025), (torch.float32, torch.float16, 32768, 1025)])
+def test_wide_rows_alone_and_among_many(xd, yd, D, n):
+    """One and two rows per workgroup (few and many rows) give a row the same bits."""
+    say(f"case: wide rows {n} x {D} {xd} to {yd}")
+    g = torch.Generator(device="cuda").manual_seed(D + n)
+    X = torch.randn((n, D), generator=g, device="cuda").to(xd)
+    m = torch.rand(D, generator=g, device="cuda") + 0.5
+    for mode, scale in ((P.PRECOND_DIAG, m), (P.PRECOND_NONE, None)):
+        Y = torch.empty((n, D), dtype=yd, device="cuda")
+        P.attr_precond_apply(X, mode, scale, True, Y)
+        few = torch.empty((3, D), dtype=yd, device="cuda")
+        P.attr_precond_apply(X[-3:], mode, scale, True, few)
+        assert torch.equal(Y[-3:], few)
+        x = X[-99:].double() * (scale.double() if scale is not None else 1.0)
+        x = x / x.norm(dim=1, keepdim=True)
+        rel, sub = (2.0 ** -11, 2.0 ** -25) if yd == torch.float16 else (1e-6, 0.0)
+        assert ((Y[-99:].double() - x).abs() <= 1.01 * rel * x.abs() + sub).all()
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
