@@ -839,18 +839,27 @@ __global__ __launch_bounds__(256) void score_rselect_kernel(
     c = collect(floor_key);  // everything above the bound
     ok = c <= RS_CAP;        // fewer than k entries is allowed
   } else {
-    // No bound yet: the k-th largest segment maximum.  k segments reach it,
-    // so at least k scores do; unless one segment holds many of the top
+    // No bound yet: a threshold that at least k and, where they differ, at most k + 8
+    // of the segment maxima reach, so at least k scores do; unless one segment holds many of the top
     // scores, few more than k do.
-    uint32_t key[RS_MAXSEG / 256];
+    // (Ballots over as many maxima per thread as the chunk has, down to a threshold
+    // that few more reach: 300 queries, 9000 x 2048, k = 1, the whole call 48 us; 62
+    // with ballots over 4096 places down to the k-th itself, 54 with a sort.)
+    auto kth_max = [&](auto per_thread) {
+      constexpr int V = decltype(per_thread)::value;
+      uint32_t key[V];
 #pragma unroll
-    for (int u = 0; u < RS_MAXSEG / 256; ++u) {
-      const int g = t + 256 * u;
-      const uint32_t x = g < n_sc ? fkey(sm[g]) : 0u;
-      key[u] = selectable(x) ? x : 0u;
-    }
-    int reach;
-    const uint32_t kth = block_kth<RS_MAXSEG / 256>([&](int u) { return key[u]; }, k, 0, kcnt, reach);
+      for (int u = 0; u < V; ++u) {
+        const int g = t + 256 * u;
+        const uint32_t x = g < n_sc ? fkey(sm[g]) : 0u;
+        key[u] = selectable(x) ? x : 0u;
+      }
+      int reach;
+      return block_kth<V>([&](int u) { return key[u]; }, k, 8, kcnt, reach);
+    };
+    const uint32_t kth = n_sc <= 256    ? kth_max(std::integral_constant<int, 1>{})
+                         : n_sc <= 1024 ? kth_max(std::integral_constant<int, 4>{})
+                                        : kth_max(std::integral_constant<int, RS_MAXSEG / 256>{});
     const uint32_t tau = kth ? kth : floor_key;
     c = collect(tau);
     ok = c <= RS_CAP;

@@ -37,7 +37,8 @@ def test_zeros_of_either_sign_are_equal(nq, n, D, dt, k):
     assert (ti == torch.tensor(want, device="cuda")).all() and (ts == 0).all()
 
 
-@pytest.mark.parametrize("nq,n,D", PLANS + [(1, 32000, 1024), (1, 600, 64), (3, 300000, 256)])
+@pytest.mark.parametrize("nq,n,D", PLANS + [(1, 32000, 1024), (1, 600, 64), (3, 300000, 256),
+                                             (130, 16385, 64), (130, 65537, 64)])
 @pytest.mark.parametrize("dt", [torch.float16, torch.float32])
 @pytest.mark.parametrize("k", [1, 10, 100, 128])
 @pytest.mark.parametrize("merge", [False, True])
