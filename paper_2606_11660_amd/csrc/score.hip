@@ -1016,10 +1016,15 @@ __device__ inline Cand wave_best(Cand c) {
 
 
 // Split-K plan with at most 256 store rows (a batch of new rows scored and
-// merged into a running list): one wave per query sums the slices of its
-// scores in slice order and takes the k best of those rows and of the
-// previous list (merge) by k rounds of wave arg-max, writing the list in
-// place.  Replaces the partition select and the merge launches.
+// merged into a running list) and k <= SMALL_SELECT_K: one wave per query sums
+// the slices of its scores in slice order and takes the k best of those rows and
+// of the previous list (merge) by k rounds of wave arg-max, writing the list in
+// place.  Replaces the partition select and the merge launches.  A round takes
+// 0.6 to 1.2 us; for larger k the threshold and the sort of the kernel below, ~10 us
+// whatever k, are faster (16 queries, rounds / threshold, the whole call: 256 x 1024 k
+// = 8 17 / 15, k = 100 112 / 19; 40 x 256 13 / 12, 78 / 22; one row of 64 10 / 14, k =
+// 12 12 / 14, k = 100 64 / 18).
+constexpr int SMALL_SELECT_K = 8;
 __global__ __launch_bounds__(64) void score_small_select_kernel(
     const float* __restrict__ spart, int64_t nqp, int64_t n_g, int n_split, int k, int merge,
     int64_t index_base, float* top_s, int64_t* top_i) {
@@ -1116,7 +1121,8 @@ __device__ inline void write_best(Cand* buf, int n, int k, float* os, int64_t* o
   }
 }
 
-// Split-K plan with more than 256 rows (a store of fewer than 32768 rows):
+// Split-K plan with more than 256 rows or a larger k (a store of fewer than 32768
+// rows; fewer than k of them pass whole):
 // one workgroup per query sums every row's slices (slice order) into registers,
 // rows u 1024 + t in thread t.  The k-th largest of the threads' best rows is
 // reached by k distinct rows, so the k best of all are at or above it; those
@@ -1664,7 +1670,7 @@ hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int
 #undef ATTR_SK
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (n_g <= 256) {
+    if (n_g <= 256 && k <= SMALL_SELECT_K) {
       hipLaunchKernelGGL(score_small_select_kernel, dim3((unsigned)n_q), dim3(64), 0, s,
                          (const float*)spart, (int64_t)plan.n_qb * SQB, n_g, plan.split, k,
                          merge, index_base, top_s, top_i);

@@ -67,3 +67,32 @@ def test_mass_ties(nq, n, D, dt, k, merge):
         S, idx = S.gather(1, order), idx.gather(1, order)
     order = torch.sort(S, dim=1, descending=True, stable=True).indices[:, :k]
     assert torch.equal(ts, S.gather(1, order)) and torch.equal(ti, idx.gather(1, order))
+
+
+@pytest.mark.parametrize("n", [1, 7, 40, 256, 257])
+@pytest.mark.parametrize("dt", [torch.float16, torch.float32])
+@pytest.mark.parametrize("k", [8, 9, 100, 128])
+@pytest.mark.parametrize("merge", [False, True])
+def test_fewer_rows_than_k(n, dt, k, merge):
+    """Stores of few rows, some of them NaN or infinite, on both sides of the small
+    store's rule: every row but NaN and -inf, then empty entries."""
+    say(f"case: few rows n={n} {dt} k={k} merge={merge}")
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    G = torch.randint(-2, 3, (n, 192), generator=g, device="cuda").to(dt)
+    Q = torch.randint(-2, 3, (5, 192), generator=g, device="cuda").to(dt)
+    Q[:, 0] = 1
+    G[n // 2, 0], G[n // 3, 0], G[0, 0] = float("nan"), -float("inf"), float("inf")
+    prev = ([3.0, 0.0, -0.0][:k], [5, 3000, 7000][:k]) if merge else None
+    ts, ti = _topk(Q, G, k, prev)
+    # (-inf for what is never selected; NaN products of inf and 0 cannot arise in column 0)
+    S = (Q.float().unsqueeze(1) * G.float()).sum(2)
+    idx = torch.arange(1000, 1000 + n, device="cuda").expand(5, n)
+    if merge:
+        s, i = (torch.tensor(x, device="cuda").expand(5, len(x)) for x in prev)
+        S, idx = torch.cat([s.float(), S], 1), torch.cat([i, idx], 1)
+    for q in range(5):
+        live = [(-s, i) for s, i in zip(S[q].tolist(), idx[q].tolist()) if s > -float("inf")]
+        want = sorted((s + 0.0, i) for s, i in live)[:k]
+        want += [(float("inf"), -1)] * (k - len(want))
+        assert ti[q].tolist() == [i for _, i in want]
+        assert ts[q].tolist() == [-s for s, _ in want]
