@@ -1016,7 +1016,7 @@ __device__ inline Cand wave_best(Cand c) {
 
 
 // Split-K plan with at most 256 store rows (a batch of new rows scored and
-// merged into a running list) and k <= SMALL_SELECT_K: one wave per query sums
+// merged into a running list) and k <= 8, or 12 for 16 rows: one wave per query sums
 // the slices of its scores in slice order and takes the k best of those rows and
 // of the previous list (merge) by k rounds of wave arg-max, writing the list in
 // place.  Replaces the partition select and the merge launches.  A round takes
@@ -1024,7 +1024,7 @@ __device__ inline Cand wave_best(Cand c) {
 // whatever k, are faster (16 queries, rounds / threshold, the whole call: 256 x 1024 k
 // = 8 17 / 15, k = 100 112 / 19; 40 x 256 13 / 12, 78 / 22; one row of 64 10 / 14, k =
 // 12 12 / 14, k = 100 64 / 18).
-constexpr int SMALL_SELECT_K = 8;
+inline bool small_select(int64_t n_g, int k) { return n_g <= 256 && k <= (n_g <= 16 ? 12 : 8); }
 __global__ __launch_bounds__(64) void score_small_select_kernel(
     const float* __restrict__ spart, int64_t nqp, int64_t n_g, int n_split, int k, int merge,
     int64_t index_base, float* top_s, int64_t* top_i) {
@@ -1670,7 +1670,7 @@ hipError_t launch_score_topk(bool f16, const ScorePlan& plan, const void* Q, int
 #undef ATTR_SK
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (n_g <= 256 && k <= SMALL_SELECT_K) {
+    if (small_select(n_g, k)) {
       hipLaunchKernelGGL(score_small_select_kernel, dim3((unsigned)n_q), dim3(64), 0, s,
                          (const float*)spart, (int64_t)plan.n_qb * SQB, n_g, plan.split, k,
                          merge, index_base, top_s, top_i);
